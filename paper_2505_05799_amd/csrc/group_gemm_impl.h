@@ -319,6 +319,13 @@ struct __align__(16) Smem {
 // that no queue state stays in registers across a tile.  Thread 0 of a
 // workgroup claims tiles: first from the queue of its own XCD, then from the
 // others in turn once that is empty (sm.qi counts the queues tried).
+// A workgroup's first tile is fixed: the j-th workgroup of an XCD starts on
+// tile j of its queue, and the head counter deals out the tiles after those
+// (queue_first).  The launch's workgroups all start within a microsecond, and
+// claiming their first tiles from eight counters cost each a chain of memory
+// round trips behind atomics to one address, which are served one after the
+// other: forwards of 13, 32 and 256 tokens (DeepSeek-V2-Lite-, Mixtral- and
+// Qwen1.5-shaped) 139, 465 and 127 us, with fixed first tiles 109, 364, 121.
 struct TileQueue {
   int32_t* ctr;       // [kXcd][4] head counters (field 0)
   const int4* flat;   // [kXcd][fcap] tile entries
@@ -336,17 +343,24 @@ __device__ inline TileQueue tile_queue(const GemmArgs& a, int pidx) {
   Q.x0 = blockIdx.x % kXcd;  // workgroups are dealt round-robin over the XCDs
   return Q;
 }
-// claim the next index of the current queue (thread 0).  A queue whose head
-// has already passed its tile count is skipped after a plain load: once the
-// tiles run out, every workgroup would otherwise add to every head counter,
-// and those same-address atomics serialize in L2 (hundreds per counter).
-// Heads only grow, so a stale read can only cost one extra atomic.
+// tiles of queue x that are not dealt out by its head counter: one for every
+// workgroup that starts on it
+__device__ inline int queue_first(int x) {
+  return (int)(gridDim.x / kXcd) + ((unsigned)x < gridDim.x % kXcd ? 1 : 0);
+}
+// claim the next index of the current queue (thread 0).  A queue without
+// tiles past the first ones is skipped without a memory access, and one whose
+// head has already passed its tile count after a plain load: once the tiles
+// run out, every workgroup would otherwise add to every head counter, and
+// those same-address atomics serialize in L2 (hundreds per counter).  Heads
+// only grow, so a stale read can only cost one extra atomic.
 __device__ inline int pop_start(const TileQueue& Q, const Smem& sm, int qi) {
   if (qi >= kXcd) return 0;
   const int x = (Q.x0 + qi) % kXcd;
   int32_t* c = &Q.ctr[x * 4];
-  if (__hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= sm.qtotal[x]) return 0x7fffffff;
-  return atomicAdd(c, 1);
+  const int f = queue_first(x), rest = sm.qtotal[x] - f;
+  if (rest <= 0 || __hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= rest) return 0x7fffffff;
+  return f + atomicAdd(c, 1);
 }
 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
@@ -563,7 +577,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const G
   if (tid == 0 && sm.qi < kXcd) {
     const TileQueue Q = tile_queue(a, PHASE == kPhaseRaw ? 0 : PHASE);
     const int x = (Q.x0 + sm.qi) % kXcd;
-    if (sm.qtotal[x] - sm.cur_idx > kClaimAheadMargin) spec = atomicAdd(&Q.ctr[x * 4], 1);
+    if (sm.qtotal[x] - sm.cur_idx > kClaimAheadMargin) spec = queue_first(x) + atomicAdd(&Q.ctr[x * 4], 1);
   }
   if (tid < BM) {
     const int m0 = row0 + tid;
@@ -733,10 +747,6 @@ __device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const G
         for (int nf = 0; nf < NF; ++nf) {
           touch_raw<KD>(raw[0][l][nf]);
           if constexpr (GMETA) touch(meta[0][l][nf]);
-          if constexpr (KBI == 2) {
-            touch_raw<KD>(raw[KBI - 1][l][nf]);
-            if constexpr (GMETA) touch(meta[KBI - 1][l][nf]);
-          }
         }
     }
 #pragma unroll
@@ -1381,9 +1391,18 @@ __global__ void __launch_bounds__(kThreads, 2) group_gemm_kernel(GemmArgs a) {
   {
     const TileQueue Q = tile_queue(a, PHASE == kPhaseRaw ? 0 : PHASE);
     if (threadIdx.x < kXcd) sm.qtotal[threadIdx.x] = min(Q.ctr[threadIdx.x * 4 + 1], a.fcap);
-    if (threadIdx.x == 0) { sm.qi = 0; sm.cur_idx = 0; }
+    // the first tile's entry comes with the tile counts (in bounds: a queue
+    // has room for more tiles than an XCD has workgroups)
+    const int first = (int)blockIdx.x / kXcd;
+    int4 e;
+    if (threadIdx.x == 0) e = Q.flat[(int64_t)Q.x0 * Q.fcap + first];
     __syncthreads();
-    if (threadIdx.x == 0) claim_next<false>(Q, sm);
+    if (threadIdx.x == 0) {
+      sm.qi = 0;
+      sm.cur_idx = first;
+      if (first < sm.qtotal[Q.x0]) sm.entry = e;
+      else claim_from<false>(Q, sm, 0x7fffffff);
+    }
     __syncthreads();
   }
   for (;;) {
