@@ -138,6 +138,30 @@ bool activations_fit(const BlockInfo& bi, int64_t T) {
   return T * bi.H * 2 < lim && T * bi.k * bi.F * 2 < lim && (int64_t)bi.nsh * T * bi.Fsh * 2 < lim;
 }
 
+// Upper bound on a launch's planned tiles: 64 rows by 128 channels (gate|up) or
+// 256 (down, single linears) is the smallest tile of a group with more than 32
+// rows; smaller groups have wider ones.
+int64_t tiles_bound(int64_t groups, int64_t rows, int n, int bn) {
+  return (groups + rows / 64) * ((n + bn - 1) / bn);
+}
+// The narrow form takes launches with few tiles, and those up to kNarrowTiles
+// whose tiles stream many weight bytes.
+bool narrow_launch(int64_t tiles, int64_t weight_bytes) {
+  return tiles <= kNarrowFew || (tiles <= kNarrowTiles && weight_bytes >= tiles * kNarrowBytes);
+}
+// Whether the block's Group-GEMM launches take the narrow form (decided on the
+// gate|up launch; the routed experts' weights count by the share of experts
+// that can have tokens).
+bool narrow_block(const BlockInfo& bi, int64_t T) {
+  const int64_t P = T * bi.k, live = std::min<int64_t>(bi.E, P), sh = (int64_t)bi.nsh * T;
+  const int64_t up = tiles_bound(live, P, bi.F, 128) + tiles_bound(bi.nsh, sh, bi.Fsh, 128);
+  const int64_t down = tiles_bound(live, P, bi.H, 256) + tiles_bound(bi.nsh, sh, bi.H, 256);
+  int64_t wr = 0, ws = 0;
+  for (int g = 0; g < bi.G; ++g)
+    (g < bi.E ? wr : ws) += 2 * codes_bytes(bi.kinds[g][0], g < bi.E ? bi.F : bi.Fsh, bi.H);
+  return down <= kNarrowTiles && narrow_launch(up, wr / bi.E * live + ws);
+}
+
 WsLayout layout_of(const BlockInfo& bi, int T) {
   WsLayout L;
   size_t o = 0;
@@ -431,10 +455,11 @@ mxmoe_status mxmoe_linear_forward(const mxmoe_linear* L, mxmoe_dtype act, const 
   const int grid = group_gemm_grid(current_device());
   XPrep nox;
   memset(&nox, 0, sizeof(nox));
+  const bool narrow = narrow_launch(tiles_bound(1, m, L->n, 256), codes_bytes(kd, L->n, L->k));
   hipError_t e = launch_plan(nullptr, 1, 1, m, nullptr, nullptr, m, dl, nullptr, ga.plan, w.qcap, w.fcap, w.pfloats,
-                             nullptr, grid, nox, stream);
+                             nullptr, grid, narrow, nox, stream);
   if (e != hipSuccess) return MXMOE_ERR_HIP;
-  return hip_status(launch_group_gemm(ga, 2, grid, stream));
+  return hip_status(launch_group_gemm(ga, 2, grid, narrow, stream));
 }
 
 // -------------------------------------------------------- MoE block
@@ -616,6 +641,7 @@ mxmoe_status mxmoe_moe_forward_ex(const mxmoe_block* B, const void* block_table,
                           at<int32_t>(workspace, L.status), at<int32_t>(workspace, L.chunk_counts),
                           at<int32_t>(workspace, L.chunk_bad), &rm, stream));
   }
+  const bool narrow = narrow_block(bi, T);
   DevLinear none;
   memset(&none, 0, sizeof(none));
   const int grid = group_gemm_grid(current_device());
@@ -658,7 +684,7 @@ mxmoe_status mxmoe_moe_forward_ex(const mxmoe_block* B, const void* block_table,
   if (xp.q8) xp.r8 = at<float>(workspace, L.rxs8);
   if (xp.q4) xp.r4 = at<float>(workspace, L.rxs4);
   MX_CHECK(launch_plan(experts, bi.E, bi.G, T, counts, offsets, -1, none, mask, plan, L.qcap, L.fcap, L.pfloats,
-                       down_qmax, grid, xp, stream));
+                       down_qmax, grid, narrow, xp, stream));
   GemmArgs ga;
   memset(&ga, 0, sizeof(ga));
   ga.experts = experts;
@@ -714,7 +740,7 @@ mxmoe_status mxmoe_moe_forward_ex(const mxmoe_block* B, const void* block_table,
   ga.xsf6 = at<float>(workspace, L.xsf6);
   MX_EVENT(1);
   MX_EVENT(2);
-  MX_CHECK(launch_group_gemm(ga, 0, grid, stream));
+  MX_CHECK(launch_group_gemm(ga, 0, grid, narrow, stream));
   MX_EVENT(3);
   MX_EVENT(4);
   if (bi.any_hq || bi.any_hmx)
@@ -746,7 +772,7 @@ mxmoe_status mxmoe_moe_forward_ex(const mxmoe_block* B, const void* block_table,
   }
   MX_EVENT(5);
   MX_EVENT(6);
-  MX_CHECK(launch_group_gemm(ga, 1, grid, stream));
+  MX_CHECK(launch_group_gemm(ga, 1, grid, narrow, stream));
   MX_EVENT(7);
   MX_EVENT(8);
   if (!(opts && opts->skip_combine))

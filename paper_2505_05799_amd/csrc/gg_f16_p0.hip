@@ -2,5 +2,5 @@
 #include "group_gemm_impl.h"
 
 namespace mxmoe {
-MXMOE_GG_LAUNCHER(gg_f16_p0, MXMOE_F16, 0)
+MXMOE_GG_LAUNCHER(gg_f16_p0, group_gemm_kernel, MXMOE_F16, 0)
 }  // namespace mxmoe

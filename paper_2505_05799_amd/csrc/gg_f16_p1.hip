@@ -2,5 +2,5 @@
 #include "group_gemm_impl.h"
 
 namespace mxmoe {
-MXMOE_GG_LAUNCHER(gg_f16_p1, MXMOE_F16, 1)
+MXMOE_GG_LAUNCHER(gg_f16_p1, group_gemm_kernel, MXMOE_F16, 1)
 }  // namespace mxmoe

@@ -2,5 +2,5 @@
 #include "group_gemm_impl.h"
 
 namespace mxmoe {
-MXMOE_GG_LAUNCHER(gg_f16_raw, MXMOE_F16, kPhaseRaw)
+MXMOE_GG_LAUNCHER(gg_f16_raw, group_gemm_kernel, MXMOE_F16, kPhaseRaw)
 }  // namespace mxmoe

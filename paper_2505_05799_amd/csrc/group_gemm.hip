@@ -53,7 +53,7 @@ __global__ void __launch_bounds__(1024) plan_kernel(const DevExpert* __restrict_
                                                     const int32_t* __restrict__ offsets, int raw_m,
                                                     DevLinear raw_lin, MaskBits mask, int32_t* __restrict__ plan,
                                                     int qcap, int fcap, int64_t pfloats,
-                                                    int32_t* __restrict__ down_qmax, int nwg, XPrep xp,
+                                                    int32_t* __restrict__ down_qmax, int nwg, int nsub, XPrep xp,
                                                     TileCosts tc) {
   // workgroups 1.. encode x, one row per wavefront (grid-stride); the plan
   // below runs on workgroup 0 alone
@@ -336,7 +336,7 @@ __global__ void __launch_bounds__(1024) plan_kernel(const DevExpert* __restrict_
       if (tiles > 0) atomicAdd(&s_ng[ph], 1);
     }
     int32_t* cnt = plan + PL.cnt + (int64_t)ph * kSplitExtra;
-    for (int i = tid; i < s_used[ph]; i += blockDim.x) cnt[i] = 0;
+    for (int i = tid; i < s_used[ph] * nsub; i += blockDim.x) cnt[i] = 0;
   }
   lds_barrier();
   // 4. rank the groups by decreasing tile cost (ties: lower group first):
@@ -560,7 +560,7 @@ void tile_costs_get(TileCosts* out) {
 
 hipError_t launch_plan(const DevExpert* experts, int E, int G, int T, const int32_t* counts,
                        const int32_t* offsets, int raw_m, const DevLinear& raw_lin, const uint32_t* mask_words,
-                       int32_t* plan, int qcap, int fcap, int64_t pfloats, int32_t* down_qmax, int nwg,
+                       int32_t* plan, int qcap, int fcap, int64_t pfloats, int32_t* down_qmax, int nwg, bool narrow,
                        const XPrep& xp, hipStream_t s) {
   MaskBits mb;
   for (int i = 0; i < 64; ++i) mb.w[i] = mask_words ? mask_words[i] : 0xffffffffu;
@@ -571,11 +571,17 @@ hipError_t launch_plan(const DevExpert* experts, int E, int G, int T, const int3
   TileCosts tc;
   tile_costs_get(&tc);
   hipLaunchKernelGGL(plan_kernel, dim3(1 + nxb), dim3(1024), 0, s, experts, E, G, T, counts, offsets, raw_m, raw_lin,
-                     mb, plan, qcap, fcap, pfloats, down_qmax, nwg < 1 ? 1 : nwg, xp, tc);
+                     mb, plan, qcap, fcap, pfloats, down_qmax, nwg < 1 ? 1 : nwg, narrow ? 4 : 1, xp, tc);
   return hipGetLastError();
 }
 
-hipError_t launch_group_gemm(const GemmArgs& a, int phase, int grid, hipStream_t s) {
+hipError_t launch_group_gemm(const GemmArgs& a, int phase, int grid, bool narrow, hipStream_t s) {
+  if (narrow) {
+    grid = grid / 2 * kNarrowWgs;
+    if (a.act == MXMOE_BF16)
+      return phase == 0 ? gg_bf16_n0(a, grid, s) : (phase == 1 ? gg_bf16_n1(a, grid, s) : gg_bf16_nraw(a, grid, s));
+    return phase == 0 ? gg_f16_n0(a, grid, s) : (phase == 1 ? gg_f16_n1(a, grid, s) : gg_f16_nraw(a, grid, s));
+  }
   if (a.act == MXMOE_BF16)
     return phase == 0 ? gg_bf16_p0(a, grid, s) : (phase == 1 ? gg_bf16_p1(a, grid, s) : gg_bf16_raw(a, grid, s));
   return phase == 0 ? gg_f16_p0(a, grid, s) : (phase == 1 ? gg_f16_p1(a, grid, s) : gg_f16_raw(a, grid, s));

@@ -39,7 +39,8 @@
 //   wNg128: the 16-bit operand is formed exactly.  bf16 activations: a packed
 //           integer add turns the codes of two slots into bf16 values
 //           c + (q - z), c = 128 + 2^N - 1, and the row sums R of the staged
-//           activations (computed by an MFMA against ones) remove c * R.  fp16
+//           activations (brought along with them, or computed by an MFMA
+//           against ones in the narrow form) remove c * R.  fp16
 //           activations: the same bit pattern in fp16 minus 1024 + 2^N - 1 gives
 //           q - z exactly.  8-bit codes are converted through fp32.  Each
 //           128-wide group has its own fp16 scale s_g: the running sum Q is kept
@@ -67,6 +68,9 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 
+// (always inlined: a call would pass LDS by generic address and spill around it)
+#define MXMOE_INL __device__ __attribute__((always_inline)) inline
+
 constexpr int kThreads = 256;
 constexpr int kPhaseRaw = 2;
 constexpr int KC = 128;        // k per stage = one weight group
@@ -88,11 +92,32 @@ __host__ __device__ constexpr int cfg_bn(int c, int phase) { return 64 * cfg_nf(
 // groups outside the down phase (its two linears' 32-byte operands do not fit
 // next to 128-row accumulators), which keeps every kernel within its register
 // budget.  phase: 0 gate|up (and single linears), 1 down.
-__host__ __device__ inline int pick_cfg(int m, int kind, int phase) {
+__host__ MXMOE_INL int pick_cfg(int m, int kind, int phase) {
   const int c = m <= 16 ? CFG_S : (m <= 32 ? CFG_T : (m <= 64 ? CFG_M : CFG_L));
   const bool cap = kind == K_W4A4G || kind == K_MXFP4 || (kind == K_F8A8 && phase != 1);
   return (cap && c == CFG_L) ? CFG_M : c;
 }
+
+// The narrow form of a launch with few tiles (kNarrowFew, kNarrowTiles): every
+// planned tile is claimed as four items that cut its output, all of them with
+// NF = 1 (gate|up) or 2 (down, single linears) channel fragments per
+// wavefront: a 16- or 32-row tile in four channel quarters, a 64- or 128-row
+// tile in two row halves (32 or 64 rows) of two channel halves each.  Such a
+// launch is bound by round trips to memory (each about 1 us), not by a rate:
+// more, smaller items bring more of the chip to the weights, and the items
+// keep more of them in flight (four 128-wide k blocks where the rows fit, the
+// first of them loaded ahead of the row data).  One token of the Qwen1.5-
+// shaped block: gate|up 26 -> 11 us, down 40 -> 14 us; a 31-row w4g128 linear
+// of 14336 x 4096: 49 -> 19 us.  Three workgroups per CU: at four the register
+// budget of 128 spills (Mixtral-shaped, 32 tokens: 248 against 255 us).
+// Item i of planned configuration c:
+constexpr int kNarrowLog = 2;
+constexpr int kNarrowWgs = 3;  // resident workgroups per CU
+
+__host__ __device__ constexpr int narrow_nf(int phase) { return phase == 0 ? 1 : 2; }
+MXMOE_INL int narrow_bn(int c, int bn) { return c < CFG_M ? 4 * bn : 2 * bn; }
+MXMOE_INL int narrow_row0(int c, int mt, int i, int bm) { return c < CFG_M ? mt * bm : (2 * mt + (i >> 1)) * bm; }
+MXMOE_INL int narrow_ch0(int c, int nt, int i, int bn) { return c < CFG_M ? (4 * nt + i) * bn : (2 * nt + (i & 1)) * bn; }
 
 // Super-tile geometry of a group of mt x nt tiles: sm x sn tiles per super-tile
 // (sm = min(mt, 8), sn = min(nt, 64 / sm)), nsm x nsn super-tiles, super-tile
@@ -101,7 +126,7 @@ __host__ __device__ inline int pick_cfg(int m, int kind, int phase) {
 struct SuperDims { int sm, sn, nsm, nsn; };
 
 // ---------------------------------------------------------- MFMA helpers
-template <int ACT> __device__ inline f32x4 mfma16(u32x4 a, u32x4 b, f32x4 c) {
+template <int ACT> MXMOE_INL f32x4 mfma16(u32x4 a, u32x4 b, f32x4 c) {
   if constexpr (ACT == MXMOE_BF16)
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b),
                                                    c, 0, 0, 0);
@@ -110,12 +135,12 @@ template <int ACT> __device__ inline f32x4 mfma16(u32x4 a, u32x4 b, f32x4 c) {
                                                   c, 0, 0, 0);
 }
 
-__device__ inline float act_to_f32(uint16_t b, int act) {
+MXMOE_INL float act_to_f32(uint16_t b, int act) {
   if (act == MXMOE_BF16) return __uint_as_float(((uint32_t)b) << 16);
   return (float)__builtin_bit_cast(_Float16, b);
 }
 // fp32 -> activation dtype, round to nearest even (NaN stays NaN)
-template <int ACT> __device__ inline uint16_t f32_to_act(float f) {
+template <int ACT> MXMOE_INL uint16_t f32_to_act(float f) {
   if constexpr (ACT == MXMOE_BF16)
     return __builtin_bit_cast(uint16_t, (__bf16)f);
   else
@@ -129,7 +154,7 @@ template <int ACT> __device__ inline uint16_t f32_to_act(float f) {
 // instructions (about one ulp each) keeps the result within 2^-16 of the exact
 // value for |g| < 64: far below the one rounding of h to the 16-bit
 // activation dtype that follows.  silu_exp(g) = e^-g.
-__device__ inline float silu_exp(float g) {
+MXMOE_INL float silu_exp(float g) {
   return __builtin_amdgcn_exp2f(fminf(g * -1.44269502162933349609375f, 126.0f));
 }
 
@@ -137,41 +162,52 @@ __device__ inline float silu_exp(float g) {
 // Low-bit kinds and w8a8 prefetch a whole 128-wide k block (8-32 bytes per
 // lane); the 16-bit-operand wide kinds (w16, w8g: 32-64 bytes per lane) stream
 // one MFMA step at a time.
-template <int KD> constexpr bool streamed() { return KD == K_W16 || KD == K_W8G; }
+// (the narrow items, with two fragments per wavefront, hold whole k blocks of
+// every kind)
+template <int KD, bool NAR> constexpr bool streamed() { return !NAR && (KD == K_W16 || KD == K_W8G); }
 template <int KD> struct Raw { u32x4 d[1]; };
 template <> struct Raw<K_W2G> { u32x2 d; };
 template <> struct Raw<K_W3G> { uint32_t d[3]; };
 template <> struct Raw<K_W8A8> { u32x4 d[2]; };
+template <> struct Raw<K_W8G> { u32x4 d[2]; };
+template <> struct Raw<K_W16> { u32x4 d[4]; };
 template <> struct Raw<K_F8A8> { u32x4 d[2]; };
 template <> struct Raw<K_W4A4F6> { u32x4 d0; u32x2 d1; };  // 24 bytes: 32 e2m3 codes
 
 // loads through the global address space (the pointers come from the block
 // table, so the compiler cannot infer it and would emit flat loads)
-template <typename V> __device__ inline V gload(const void* p) {
+template <typename V> MXMOE_INL V gload(const void* p) {
   typedef __attribute__((address_space(1))) const V GV;
   return *(GV*)p;
 }
 
-template <int KD> __device__ inline void load_raw(Raw<KD>& r, const uint8_t* p) {
-  if constexpr (KD == K_W2G) {
+template <int KD> MXMOE_INL void load_raw(Raw<KD>& r, const uint8_t* p) {
+  if constexpr (KD == K_W16) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) r.d[j] = gload<u32x4>(p + 16 * j);
+  } else if constexpr (KD == K_W2G) {
     r.d = gload<u32x2>(p);
   } else if constexpr (KD == K_W3G) {  // 12-byte lanes: 4-byte aligned
     r.d[0] = gload<uint32_t>(p);
     r.d[1] = gload<uint32_t>(p + 4);
     r.d[2] = gload<uint32_t>(p + 8);
-  } else if constexpr (KD == K_W8A8 || KD == K_F8A8) {
+  } else if constexpr (KD == K_W8A8 || KD == K_F8A8 || KD == K_W8G) {
     r.d[0] = gload<u32x4>(p);
     r.d[1] = gload<u32x4>(p + 16);
   } else if constexpr (KD == K_W4A4F6) {  // 24-byte lanes: 8-byte aligned
     r.d0 = gload<u32x4>(p);
     r.d1 = gload<u32x2>(p + 16);
-  } else if constexpr (!streamed<KD>()) {
+  } else {
     r.d[0] = gload<u32x4>(p);
   }
 }
+// loads of a fragment's k block
+template <int KD> constexpr int raw_loads() {
+  return KD == K_W16 ? 4 : (KD == K_W3G ? 3 : ((KD == K_W8A8 || KD == K_F8A8 || KD == K_W4A4F6 || KD == K_W8G) ? 2 : 1));
+}
 
 // streamed kinds: the lane's bytes of MFMA step j
-template <int KD> __device__ inline u32x4 load_step(const uint8_t* p, int j) {
+template <int KD> MXMOE_INL u32x4 load_step(const uint8_t* p, int j) {
   if constexpr (KD == K_W8G) {
     const u32x2 v = gload<u32x2>(p + 8 * j);
     return u32x4{v[0], v[1], 0u, 0u};
@@ -184,18 +220,19 @@ template <int KD> __device__ inline u32x4 load_step(const uint8_t* p, int j) {
 // (loads complete in issue order), leaving LDS and export counters alone.
 // An empty statement that reads a value: the compiler waits for the loads of
 // its registers before it.
-__device__ inline void touch(uint32_t v) { asm volatile("" ::"v"(v)); }
-__device__ inline void touch(const u32x2& v) { asm volatile("" ::"v"(v)); }
-__device__ inline void touch(const u32x4& v) { asm volatile("" ::"v"(v)); }
-template <int KD> __device__ inline void touch_raw(const Raw<KD>& r) {
+MXMOE_INL void touch(uint32_t v) { asm volatile("" ::"v"(v)); }
+MXMOE_INL void touch(const u32x2& v) { asm volatile("" ::"v"(v)); }
+MXMOE_INL void touch(const u32x4& v) { asm volatile("" ::"v"(v)); }
+template <int KD> MXMOE_INL void touch_raw(const Raw<KD>& r) {
   if constexpr (KD == K_W2G) touch(r.d);
   else if constexpr (KD == K_W3G) { touch(r.d[0]); touch(r.d[1]); touch(r.d[2]); }
   else if constexpr (KD == K_W4A4F6) { touch(r.d0); touch(r.d1); }
-  else if constexpr (KD == K_W8A8 || KD == K_F8A8) { touch(r.d[0]); touch(r.d[1]); }
+  else if constexpr (KD == K_W8A8 || KD == K_F8A8 || KD == K_W8G) { touch(r.d[0]); touch(r.d[1]); }
+  else if constexpr (KD == K_W16) { touch(r.d[0]); touch(r.d[1]); touch(r.d[2]); touch(r.d[3]); }
   else touch(r.d[0]);
 }
 
-template <int N> __device__ inline void wait_vmem() {
+template <int N> MXMOE_INL void wait_vmem() {
   static_assert(N >= 0 && N < 64, "vmcnt is six bits");
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
@@ -204,7 +241,7 @@ template <int N> __device__ inline void wait_vmem() {
 // wavefront's LDS operations only.  __syncthreads() carries a fence that also
 // drains every outstanding global load, which would stall the weight prefetch;
 // the direct-to-LDS stage loads are covered by wait_vmem before this barrier.
-__device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+MXMOE_INL void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // Device-scope coherent 16-byte store and load (scope bit sc1), used for
 // partial sums that another XCD reads within the same launch.  The store is
@@ -212,17 +249,17 @@ __device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_b
 // may overwrite the data registers in the next instruction, and a store wider
 // than 8 bytes still reads them then.  The load is asynchronous: wait_loaded()
 // must run before its result is used.
-__device__ inline void store_coherent(float* p, u32x4 v) {
+MXMOE_INL void store_coherent(float* p, u32x4 v) {
   asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
 }
-__device__ inline u32x4 load_coherent(const float* p) {
+MXMOE_INL u32x4 load_coherent(const float* p) {
   u32x4 v;
   asm volatile("global_load_dwordx4 %0, %1, off sc1" : "=v"(v) : "v"(p) : "memory");
   return v;
 }
 // Wait for every outstanding vector-memory load; the registers of v are tied
 // to the wait so that no use of them is scheduled before it.
-template <int N> __device__ inline void wait_loaded(u32x4 (&v)[N]) {
+template <int N> MXMOE_INL void wait_loaded(u32x4 (&v)[N]) {
   if constexpr (N == 1) asm volatile("s_waitcnt vmcnt(0)" : "+v"(v[0])::"memory");
   else if constexpr (N == 2) asm volatile("s_waitcnt vmcnt(0)" : "+v"(v[0]), "+v"(v[1])::"memory");
   else if constexpr (N == 4)
@@ -237,7 +274,7 @@ template <int N> __device__ inline void wait_loaded(u32x4 (&v)[N]) {
 // bias constant b = 2^N - 1 of the exact magic-number dequantization
 template <int KD> constexpr int wbias() { return KD == K_W2G ? 3 : (KD == K_W3G ? 7 : 15); }
 
-template <int ACT> __device__ inline uint32_t pack_exact(float lo, float hi) {
+template <int ACT> MXMOE_INL uint32_t pack_exact(float lo, float hi) {
   if constexpr (ACT == MXMOE_BF16)  // small integers: truncation to bf16 is exact
     return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
   else
@@ -247,7 +284,7 @@ template <int ACT> __device__ inline uint32_t pack_exact(float lo, float hi) {
 // 16-bit weight operand of MFMA step j (8 slots) for the lane's channel.
 // bz: per-group constant (bias pair for 2/3/4-bit codes, zero point for 8-bit).
 template <int KD, int ACT>
-__device__ inline u32x4 wfrag16(const Raw<KD>& r, u32x4 step, int j, uint32_t bz, float zf) {
+MXMOE_INL u32x4 wfrag16(const Raw<KD>& r, u32x4 step, int j, uint32_t bz, float zf) {
   u32x4 o;
   if constexpr (KD == K_W16) {
     o = step;
@@ -284,7 +321,7 @@ __device__ inline u32x4 wfrag16(const Raw<KD>& r, u32x4 step, int j, uint32_t bz
 }
 
 // int8 weight operand of MFMA step j (16 slots)
-template <int KD> __device__ inline i32x4 wfrag8(const Raw<KD>& r, u32x4 step, int j) {
+template <int KD> MXMOE_INL i32x4 wfrag8(const Raw<KD>& r, u32x4 step, int j) {
   if constexpr (KD == K_W8A8) {
     return __builtin_bit_cast(i32x4, r.d[j]);
   } else {
@@ -299,8 +336,10 @@ template <int KD> __device__ inline i32x4 wfrag8(const Raw<KD>& r, u32x4 step, i
 }
 
 // ------------------------------------------------------------- LDS stage
-struct __align__(16) Smem {
-  uint8_t act[2][STAGE_BYTES];   // activation rows of the tile, one 128-wide k block per stage
+// SB: bytes of a stage buffer; WS: channel scales of a tile
+template <int SB, int WS> struct __align__(16) SmemT {
+  static constexpr int kStage = SB;
+  uint8_t act[2][SB];            // activation rows of the tile, one 128-wide k block per stage
   float rsum[2][BM_MAX];         // per-row sums of a stage (bf16 weight-only kinds)
   int32_t rowsrc[BM_MAX];        // activation row index of every tile row
   int32_t rowout[BM_MAX];        // output row index of every tile row, -1 past the group's rows
@@ -312,8 +351,10 @@ struct __align__(16) Smem {
   int32_t last;                  // split-K: this workgroup finishes the output tile
   int32_t spec;                  // index claimed ahead on queue qi, or -1
   int32_t cur_idx;               // queue index of the tile in progress
-  float wsc[512];                // per-channel weight scales of the tile's channels (a8/a4, FP8, FP6)
+  float wsc[WS];                 // per-channel weight scales of the tile's channels (a8/a4, FP8, FP6)
 };
+
+template <bool NAR> using Smem = SmemT<NAR ? STAGE_BYTES / 2 : STAGE_BYTES, NAR ? 128 : 512>;
 
 // Tile queues of one phase, rebuilt from the kernel arguments where needed so
 // that no queue state stays in registers across a tile.  Thread 0 of a
@@ -332,7 +373,7 @@ struct TileQueue {
   int fcap;
   int x0;             // queue of this workgroup's XCD
 };
-__device__ inline TileQueue tile_queue(const GemmArgs& a, int pidx) {
+MXMOE_INL TileQueue tile_queue(const GemmArgs& a, int pidx) {
   int32_t* plan = a.plan;
   asm volatile("" : "+s"(plan));  // recomputed here, not kept live from an earlier use
   const PlanLayout PL = plan_layout(a.G, a.qcap, a.fcap);
@@ -345,7 +386,7 @@ __device__ inline TileQueue tile_queue(const GemmArgs& a, int pidx) {
 }
 // tiles of queue x that are not dealt out by its head counter: one for every
 // workgroup that starts on it
-__device__ inline int queue_first(int x) {
+MXMOE_INL int queue_first(int x) {
   return (int)(gridDim.x / kXcd) + ((unsigned)x < gridDim.x % kXcd ? 1 : 0);
 }
 // claim the next index of the current queue (thread 0).  A queue without
@@ -354,7 +395,7 @@ __device__ inline int queue_first(int x) {
 // run out, every workgroup would otherwise add to every head counter, and
 // those same-address atomics serialize in L2 (hundreds per counter).  Heads
 // only grow, so a stale read can only cost one extra atomic.
-__device__ inline int pop_start(const TileQueue& Q, const Smem& sm, int qi) {
+template <class SM> MXMOE_INL int pop_start(const TileQueue& Q, const SM& sm, int qi) {
   if (qi >= kXcd) return 0;
   const int x = (Q.x0 + qi) % kXcd;
   int32_t* c = &Q.ctr[x * 4];
@@ -363,7 +404,12 @@ __device__ inline int pop_start(const TileQueue& Q, const Smem& sm, int qi) {
   return f + atomicAdd(c, 1);
 }
 
-typedef __attribute__((address_space(3))) void* lds_ptr_t;
+typedef __attribute__((address_space(3))) const void* lds_ptr_t;
+// LDS byte address of the workgroup's Smem (fields by offsetof: a cast of a
+// computed address can leave the compiler without its address space)
+template <class SM> MXMOE_INL uint32_t lds_base(const SM& sm) {
+  return (uint32_t)reinterpret_cast<uintptr_t>((lds_ptr_t)&sm);
+}
 
 // Stage one k block of BM rows into act[buf] with direct global->LDS loads.
 // A row's k block is RB bytes: 256 for 16-bit rows (16 chunks, chunk c stored
@@ -384,8 +430,8 @@ template <int RB_, int BM> struct StageOffs {
   uint32_t off[PER_WAVE];
 };
 
-template <int RB, int BM>
-__device__ inline void stage_offsets(StageOffs<RB, BM>& so, const Smem& sm, int64_t row_bytes, int wave, int lane) {
+template <int RB, int BM, class SM>
+MXMOE_INL void stage_offsets(StageOffs<RB, BM>& so, const SM& sm, int64_t row_bytes, int wave, int lane) {
   using S = StageOffs<RB, BM>;
 #pragma unroll
   for (int i = 0; i < S::PER_WAVE; ++i) {
@@ -406,16 +452,16 @@ __device__ inline void stage_offsets(StageOffs<RB, BM>& so, const Smem& sm, int6
 // stage.
 // The base address is uniform by construction.  With UP it passes through
 // readfirstlane, so that the scalar operand does not depend on the compiler
-// proving that; the mxfp4 tiles need it (without it the compiler keeps the
-// base in a VGPR there), the others do without (the extra copies would cost
+// proving that; the mxfp4 tiles and the narrow items need it (without it the
+// compiler keeps the base in a VGPR there), the others do without (the extra copies would cost
 // registers across the whole kernel).
-__device__ inline const uint8_t* uniform_ptr(const uint8_t* p) {
+MXMOE_INL const uint8_t* uniform_ptr(const uint8_t* p) {
   const uint64_t v = reinterpret_cast<uint64_t>(p);
   const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
   const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
   return reinterpret_cast<const uint8_t*>(((uint64_t)hi << 32) | lo);
 }
-template <bool UP = false> __device__ inline void lds_dma16(const uint8_t* base, uint32_t voff, uint32_t lds_addr) {
+template <bool UP = false> MXMOE_INL void lds_dma16(const uint8_t* base, uint32_t voff, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                :
                : "v"(voff), "s"(UP ? uniform_ptr(base) : base), "s"(lds_addr)
@@ -424,7 +470,7 @@ template <bool UP = false> __device__ inline void lds_dma16(const uint8_t* base,
 
 // The same load with device scope (sc1: past this XCD's L2), for partial sums
 // that other XCDs stored with store_coherent (base made wave-uniform).
-__device__ inline void lds_dma16_coherent(const uint8_t* base, uint32_t voff, uint32_t lds_addr) {
+MXMOE_INL void lds_dma16_coherent(const uint8_t* base, uint32_t voff, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 sc1"
                :
                : "v"(voff), "s"(uniform_ptr(base)), "s"(lds_addr)
@@ -434,7 +480,7 @@ __device__ inline void lds_dma16_coherent(const uint8_t* base, uint32_t voff, ui
 // Claim the next tile and load its entry straight into sm.entry (thread 0;
 // the caller waits for the load with its vector-memory count), or mark the
 // end with group -1.  The first claim of a workgroup uses a plain load.
-template <bool DMA> __device__ inline void claim_from(const TileQueue& Q, Smem& sm, int idx) {
+template <bool DMA, class SM> MXMOE_INL void claim_from(const TileQueue& Q, SM& sm, int idx) {
   int qi = sm.qi;
   while (qi < kXcd) {
     const int x = (Q.x0 + qi) % kXcd;
@@ -442,7 +488,7 @@ template <bool DMA> __device__ inline void claim_from(const TileQueue& Q, Smem& 
       sm.qi = qi;
       sm.cur_idx = idx;
       if constexpr (DMA) {
-        const uint32_t lds = (uint32_t)reinterpret_cast<uintptr_t>((lds_ptr_t)&sm.entry);
+        const uint32_t lds = lds_base(sm) + (uint32_t)offsetof(SM, entry);
         lds_dma16(reinterpret_cast<const uint8_t*>(Q.flat), (uint32_t)(((int64_t)x * Q.fcap + idx) * 16),
                   __builtin_amdgcn_readfirstlane(lds));
       } else {
@@ -456,8 +502,36 @@ template <bool DMA> __device__ inline void claim_from(const TileQueue& Q, Smem& 
   sm.qi = qi;
   sm.entry.x = -1;  // only the group field is read when no tile is left
 }
-template <bool DMA> __device__ inline void claim_next(const TileQueue& Q, Smem& sm) {
+template <bool DMA, class SM> MXMOE_INL void claim_next(const TileQueue& Q, SM& sm) {
   claim_from<DMA>(Q, sm, pop_start(Q, sm, sm.qi));
+}
+// Items of the narrow form: item i is part i % 4 of tile i / 4, the tiles of
+// the XCD queues counted one queue after the other.  Workgroup b starts on
+// item b; the items past the grid are dealt out by the queues' head counters,
+// every eighth to each (no stealing: the eight run out together).  sm.qi holds
+// the number of items, sm.cur_idx the item.  (A narrow launch has few tiles,
+// and the queues that the super-tiles give are far from even then: a shared
+// expert's tiles may all lie in one.)
+template <class SM> MXMOE_INL int claim_item(const TileQueue& Q, const SM& sm) {
+  const int n = (int)gridDim.x;
+  if (sm.qi <= n) return 0x7fffffff;
+  return n + kXcd * atomicAdd(&Q.ctr[Q.x0 * 4], 1) + Q.x0;
+}
+template <bool DMA, class SM> MXMOE_INL void item_entry(const TileQueue& Q, SM& sm, int item) {
+  if (item >= sm.qi) {
+    sm.entry.x = -1;
+    return;
+  }
+  sm.cur_idx = item;
+  int t = item >> kNarrowLog, x = 0;
+  while (x < kXcd - 1 && t >= sm.qtotal[x]) t -= sm.qtotal[x++];
+  if constexpr (DMA) {
+    const uint32_t lds = lds_base(sm) + (uint32_t)offsetof(SM, entry);
+    lds_dma16<true>(reinterpret_cast<const uint8_t*>(Q.flat), (uint32_t)(((int64_t)x * Q.fcap + t) * 16),
+                    __builtin_amdgcn_readfirstlane(lds));
+  } else {
+    sm.entry = Q.flat[(int64_t)x * Q.fcap + t];
+  }
 }
 // A tile started while its queue still holds more than this many unclaimed
 // tiles claims the next one at its start (the claim's round trips then hide
@@ -467,20 +541,20 @@ constexpr int kClaimAheadMargin = 256;
 
 // sub: sub-stage of the buffer (tiles that stage two k blocks per step put
 // the second one's BM rows after the first one's)
-template <int RB, int BM>
-__device__ inline void stage_load(Smem& sm, int buf, const uint8_t* base, const StageOffs<RB, BM>& so, int kb,
+template <int RB, int BM, class SM>
+MXMOE_INL void stage_load(SM& sm, int buf, const uint8_t* base, const StageOffs<RB, BM>& so, int kb,
                                   int wave, int sub = 0) {
   using S = StageOffs<RB, BM>;
   const uint8_t* bk = base + (int64_t)kb * S::RB;  // uniform
-  const uint32_t lds0 = (uint32_t)reinterpret_cast<uintptr_t>((lds_ptr_t)sm.act[buf]) + sub * BM * RB;
+  const uint32_t lds0 = lds_base(sm) + (uint32_t)offsetof(SM, act) + (uint32_t)(buf * SM::kStage + sub * BM * RB);
 #pragma unroll
   for (int i = 0; i < S::PER_WAVE; ++i) {
     const int blk = wave + 4 * i;
-    if (blk < S::NBLK) lds_dma16<RB == 64>(bk, so.off[i], __builtin_amdgcn_readfirstlane(lds0 + blk * 1024));
+    if (blk < S::NBLK) lds_dma16<RB == 64 || SM::kStage != STAGE_BYTES>(bk, so.off[i], __builtin_amdgcn_readfirstlane(lds0 + blk * 1024));
   }
 }
 
-template <int RB> __device__ inline u32x4 act_frag(const Smem& sm, int buf, int r, int cc) {
+template <int RB, class SM> MXMOE_INL u32x4 act_frag(const SM& sm, int buf, int r, int cc) {
   return *reinterpret_cast<const u32x4*>(sm.act[buf] + r * RB + stage_swz<RB>(cc, r) * 16);
 }
 
@@ -488,28 +562,29 @@ template <int RB> __device__ inline u32x4 act_frag(const Smem& sm, int buf, int 
 // direct global->LDS load of 4 bytes per lane brings the precomputed sums of
 // rows 64w .. 64w + 63 of k block kb into sm.rsum[buf] (wavefronts
 // w < ceil(BM / 64)); rsoff: the lane's row offset (bytes) at k block 0.
-template <bool UP = false> __device__ inline void lds_dma4(const uint8_t* base, uint32_t voff, uint32_t lds_addr) {
+template <bool UP = false> MXMOE_INL void lds_dma4(const uint8_t* base, uint32_t voff, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1"
                :
                : "v"(voff), "s"(UP ? uniform_ptr(base) : base), "s"(lds_addr)
                : "memory", "m0");
 }
-// (sub-stage s of a tile of at most 64 rows takes rsum[buf][64 s ..])
-template <int BM, bool UP = false>
-__device__ inline void rowsum_load(Smem& sm, int buf, const float* rsbase, uint32_t rsoff, int kb, int wave,
+// (sub-stage s of a tile of at most RSS rows takes rsum[buf][RSS s ..])
+template <int BM, bool UP, int RSS, class SM>
+MXMOE_INL void rowsum_load(SM& sm, int buf, const float* rsbase, uint32_t rsoff, int kb, int wave,
                                    int sub = 0) {
-  if (wave * 64 < BM) {
-    const uint32_t lds = (uint32_t)reinterpret_cast<uintptr_t>((lds_ptr_t)&sm.rsum[buf][sub * 64 + wave * 64]);
+  if (wave * 64 < BM && (RSS == 64 || (threadIdx.x & 63) < RSS)) {
+    const uint32_t lds = lds_base(sm) + (uint32_t)offsetof(SM, rsum) + (uint32_t)(buf * BM_MAX + sub * RSS + wave * 64) * 4u;
     lds_dma4<UP>(reinterpret_cast<const uint8_t*>(rsbase + kb), rsoff, __builtin_amdgcn_readfirstlane(lds));
   }
 }
 
 // ---------------------------------------------------------- tile body
-template <int KD, int ACT, int CFG, int PHASE>
-__device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const GemmArgs& a, const DevExpert* ex, int g, int m_g, int mt, int ntv,
-                                int off_e, int split) {
+template <int KD, int ACT, int CFG, int PHASE, bool NAR>
+MXMOE_INL void run_tile(Smem<NAR>& sm, const GemmArgs& a, const DevExpert* ex, int g, int m_g, int mt, int ntv,
+                                int off_e, int split, int pcfg, int sub) {
+  constexpr int STAGE = Smem<NAR>::kStage;
   constexpr int MF = cfg_mf(CFG);
-  constexpr int NF = cfg_nf(CFG, PHASE == 0 ? 0 : 1);
+  constexpr int NF = NAR ? narrow_nf(PHASE == 0 ? 0 : 1) : cfg_nf(CFG, PHASE == 0 ? 0 : 1);
   constexpr int NL = PHASE == 0 ? 2 : 1;
   constexpr bool INT = kind_is_int(KD);
   constexpr bool WONLY = kind_is_wonly(KD);
@@ -520,7 +595,8 @@ __device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const G
   constexpr bool F8 = kind_is_f8(KD);                   // FP8 e4m3 operands, fp32 accumulation
   constexpr bool F6 = kind_is_f6(KD);                   // int4 codes as FP6 e2m3 operands, exact fp32 sums
   constexpr bool GMETA = kind_has_gmeta(KD);            // group metadata after each fragment block
-  constexpr bool RSLOAD = RSUM || GSC || MX;            // a per-row value per k block rides with the stage
+  constexpr bool RSMMA = RSUM && NAR;                   // ... formed by an MFMA against ones next to the tile's own
+  constexpr bool RSLOAD = (RSUM && !NAR) || GSC || MX;  // a per-row value per k block rides with the stage
   constexpr int RB = stage_rb<KD>();                    // activation bytes per row and k block
   constexpr int BM = 16 * MF;
   constexpr int BN = 64 * NF;
@@ -544,13 +620,15 @@ __device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const G
   // split-K: queued channel tile ntv = slice * (channel tiles) + channel tile;
   // the slice reduces k blocks [kb0, kb1), balanced so that every slice is
   // non-empty (the plan only slices when there are >= 6 k blocks per slice)
-  const int ntr = (N + BN - 1) / BN;
+  const int bnw = NAR ? narrow_bn(pcfg, BN) : BN;  // channels of the planned tile
+  const int ntr = (N + bnw - 1) / bnw;
   const int slice = split > 1 ? ntv / ntr : 0;
   const int nt = ntv - slice * ntr;
   const int kb0 = slice * kblocks / split;
   const int kb1 = (slice + 1) * kblocks / split;
-  const int row0 = mt * BM;
-  const int nb0 = (nt * BN) / 16 + wave * NF;   // first 16-channel block of this wavefront
+  const int row0 = NAR ? narrow_row0(pcfg, mt, sub, BM) : mt * BM;
+  const int ch0 = NAR ? narrow_ch0(pcfg, nt, sub, BN) : nt * BN;  // first channel
+  const int nb0 = ch0 / 16 + wave * NF;         // first 16-channel block of this wavefront
   int nvalid = N / 16 - nb0;
   nvalid = nvalid < 0 ? 0 : (nvalid > NF ? NF : nvalid);
 
@@ -571,88 +649,11 @@ __device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const G
     abase = reinterpret_cast<const uint8_t*>(PHASE == 1 ? (shared ? a.h_shared : a.h) : a.x);
   }
 
-  // ---- per-row data: activation source row (rows past the group repeat its
-  // last row), output row, activation scale, router gate weight
-  int spec = -1;
-  if (tid == 0 && sm.qi < kXcd) {
-    const TileQueue Q = tile_queue(a, PHASE == kPhaseRaw ? 0 : PHASE);
-    const int x = (Q.x0 + sm.qi) % kXcd;
-    if (sm.qtotal[x] - sm.cur_idx > kClaimAheadMargin) spec = queue_first(x) + atomicAdd(&Q.ctr[x * 4], 1);
-  }
-  if (tid < BM) {
-    const int m0 = row0 + tid;
-    const int m = m0 < m_g ? m0 : m_g - 1;
-    int src, out;
-    float gw = 1.f;
-    float sc = 1.f;
-    if constexpr (PHASE == 0) {
-      src = shared ? m : a.rtok[off_e + m];
-      out = shared ? (g - a.E_routed) * a.T + m : off_e + m;
-      if constexpr (F8 || F6) sc = ascale[src];
-      else if constexpr (INT && !GSC) sc = shared ? ascale[m] : (KD == K_W8A8 ? a.rxs8 : a.rxs4)[off_e + m];
-    } else if constexpr (PHASE == 1) {
-      src = shared ? (g - a.E_routed) * a.T + m : off_e + m;
-      if (shared) {
-        out = m * (a.k + a.n_shared) + a.k + (g - a.E_routed);
-        if (a.shared_w) gw = a.shared_w[(int64_t)m * a.n_shared + (g - a.E_routed)];
-      } else {
-        out = a.rslot[off_e + m];
-        gw = a.rgw[off_e + m];
-      }
-      if constexpr (INT && !GSC) sc = ascale[src];
-    } else {
-      src = m;
-      out = m;
-      if constexpr (INT && !GSC) sc = ascale[m];
-    }
-    sm.rowsrc[tid] = src;
-    sm.rowout[tid] = m0 < m_g ? out : -1;
-    sm.rowgw[tid] = gw;
-    sm.rowscale[tid] = sc;
-  }
-  if constexpr (INT && !GSC) {  // the channels' weight scales, for the epilogue
-    for (int i = tid; i < NL * BN; i += kThreads) {
-      const int l = i / BN, c = i - l * BN;
-      const int n = nt * BN + c;
-      sm.wsc[i] = n < N ? lins[l]->wscale[n] : 0.f;
-    }
-  }
-  const int64_t row_bytes = MX ? (int64_t)K / 2 : (int64_t)K * (INT ? 1 : 2);
-  if (tid == 0) sm.spec = spec;
-  __syncthreads();
-  // the tile after this one, claimed ahead: its entry comes into LDS now (every
-  // thread has read this tile's entry before the barrier above)
-  if (tid == 0 && spec >= 0) claim_from<true>(tile_queue(a, PHASE == kPhaseRaw ? 0 : PHASE), sm, spec);
-  StageOffs<RB, BM> soffs;
-  stage_offsets<RB, BM>(soffs, sm, row_bytes, wave, lane);
-  // row sums of the tile's activation rows per k block (bias-dequantized
-  // kinds, bf16): x rows in the gate|up phase, h rows in the down phase
-  const float* rsbase = nullptr;
-  uint32_t rsoff = 0;
-  if constexpr (RSLOAD) {
-    // row sums (bias-dequantized kinds), activation group scales (w4a4-g128)
-    // or the four E8M0 bytes of a row's k block (mxfp4)
-    if constexpr (MX)
-      rsbase = reinterpret_cast<const float*>(PHASE == 1 ? (shared ? a.hsmx_shared : a.hsmx) : a.xsmx);
-    else if constexpr (GSC) rsbase = PHASE == 1 ? (shared ? a.hsg_shared : a.hsg) : a.xs4g;
-    else rsbase = PHASE == 1 ? (shared ? a.rsh_shared : a.rsh) : a.rsx;
-    const int r = wave * 64 + lane;
-    rsoff = (uint32_t)sm.rowsrc[r < BM ? r : 0] * (uint32_t)kblocks * 4u;
-  }
-
-  // ---- accumulators and weight streams
+  // ---- weight streams
   typedef typename std::conditional<INT && !GSC && !F8 && !F6, i32x4, f32x4>::type AccT;
   typedef typename std::conditional<INT, i32x4, u32x4>::type OpT;
   constexpr int J = MX ? 1 : (INT ? 2 : 4);      // MFMA steps per 128-wide k block
   constexpr bool HOLD_W = NL * NF <= MF;         // hold the smaller operand set in registers
-  AccT acc[NL][NF][MF];
-#pragma unroll
-  for (int l = 0; l < NL; ++l)
-#pragma unroll
-    for (int nf = 0; nf < NF; ++nf)
-#pragma unroll
-      for (int mf = 0; mf < MF; ++mf) acc[l][nf][mf] = AccT{0, 0, 0, 0};
-
   // Uniform base of every fragment's block stream (fragments past the last
   // channel block read block 0 and are never stored) and the lane's offset.
   const uint8_t* wp[NL][NF];
@@ -676,9 +677,11 @@ __device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const G
   // Slot s of the weight registers serves k block kb + s and is refilled
   // right after its MFMAs, for the next step (no register copy).  The per-row values of the
   // second block sit at rsum[buf][64..], so tiles with them stop at 64 rows.
-  constexpr bool KBI_FITS = !streamed<KD>() && BM * RB * 2 <= STAGE_BYTES && (!RSLOAD || BM <= 64);
-  constexpr int KBI = (KBI_FITS && (PHASE == 1 || (BM <= 32 && LB <= 16) || INT)) ? 2 : 1;
+  constexpr bool KBI_FITS = !streamed<KD, NAR>() && BM * RB * 2 <= STAGE && (!RSLOAD || BM <= 64);
+  constexpr bool KBI4_FITS = NAR && BM * RB * 4 <= STAGE && (!RSLOAD || BM <= 32) && LB <= 32;
+  constexpr int KBI = KBI4_FITS ? 4 : ((KBI_FITS && (NAR || PHASE == 1 || (BM <= 32 && LB <= 16) || INT)) ? 2 : 1);
   static_assert(KBI == 1 || KBI_FITS, "two-block stage layout");
+  constexpr int RSS = KBI == 4 ? 32 : 64;  // per-row values of a staged k block
   Raw<KD> raw[KBI][NL][NF];   // low-bit kinds: next group(s), prefetched a step ahead
   u32x4 st[J][NL][NF];   // streamed kinds: step j of the k block, reloaded one block ahead
   uint32_t meta[KBI][NL][NF];
@@ -687,7 +690,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const G
   // (last = true) every lane reads the first 16 bytes of the fragment's block 0
   // instead (one cache line, result unused), so no register keeps two possible
   // values across the loop and no copy has to wait for an outstanding load.
-  auto load_group = [&](auto S, int kn, bool last) {
+  auto load_group = [&](auto S, int kn, bool last) __attribute__((always_inline)) {
     constexpr int SL = decltype(S)::value;
     const uint32_t lo = last ? 0u : loff, mo = last ? 0u : moff;
 #pragma unroll
@@ -695,11 +698,19 @@ __device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const G
 #pragma unroll
       for (int nf = 0; nf < NF; ++nf) {
         const uint8_t* blk = wp[l][nf] + (last ? 0 : (int64_t)kn * BB);  // uniform
-        if constexpr (!streamed<KD>()) load_raw<KD>(raw[SL][l][nf], blk + lo);
+        if constexpr (!streamed<KD, NAR>()) load_raw<KD>(raw[SL][l][nf], blk + lo);
         if constexpr (GMETA) meta[SL][l][nf] = gload<uint32_t>(blk + mo);
       }
   };
-  auto load_steps = [&](int kn, bool last, int j) {
+  auto load_first = [&]() __attribute__((always_inline)) {
+    load_group(std::integral_constant<int, 0>{}, kb0, false);
+    if constexpr (KBI > 1) load_group(std::integral_constant<int, 1>{}, kb0 + 1, kb0 + 1 >= kb1);
+    if constexpr (KBI > 2) {
+      load_group(std::integral_constant<int, 2>{}, kb0 + 2, kb0 + 2 >= kb1);
+      load_group(std::integral_constant<int, 3>{}, kb0 + 3, kb0 + 3 >= kb1);
+    }
+  };
+  auto load_steps = [&](int kn, bool last, int j) __attribute__((always_inline)) {
     const uint32_t lo = last ? 0u : loff;
 #pragma unroll
     for (int l = 0; l < NL; ++l)
@@ -707,6 +718,110 @@ __device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const G
       for (int nf = 0; nf < NF; ++nf)
         st[j][l][nf] = load_step<KD>(wp[l][nf] + (last ? 0 : (int64_t)kn * BB) + lo, j);
   };
+  // ---- per-row data: activation source row (rows past the group repeat its
+  // last row), output row, activation scale, router gate weight
+  int spec = -1;
+  if constexpr (NAR) {
+    // the item after this one: claimed here, so that its round trip hides
+    // behind this one's work
+    if (tid == 0) spec = claim_item(tile_queue(a, PHASE == kPhaseRaw ? 0 : PHASE), sm);
+  } else if (tid == 0 && sm.qi < kXcd) {
+    const TileQueue Q = tile_queue(a, PHASE == kPhaseRaw ? 0 : PHASE);
+    const int x = (Q.x0 + sm.qi) % kXcd;
+    if (sm.qtotal[x] - sm.cur_idx > kClaimAheadMargin) spec = queue_first(x) + atomicAdd(&Q.ctr[x * 4], 1);
+  }
+  const int m0 = row0 + tid;
+  int src = 0, out = 0;
+  float gw = 1.f;
+  float sc = 1.f;
+  if (tid < BM) {
+    const int m = m0 < m_g ? m0 : m_g - 1;
+    if constexpr (PHASE == 0) {
+      src = shared ? m : a.rtok[off_e + m];
+      out = shared ? (g - a.E_routed) * a.T + m : off_e + m;
+      if constexpr (F8 || F6) sc = ascale[src];
+      else if constexpr (INT && !GSC) sc = shared ? ascale[m] : (KD == K_W8A8 ? a.rxs8 : a.rxs4)[off_e + m];
+    } else if constexpr (PHASE == 1) {
+      src = shared ? (g - a.E_routed) * a.T + m : off_e + m;
+      if (shared) {
+        out = m * (a.k + a.n_shared) + a.k + (g - a.E_routed);
+        if (a.shared_w) gw = a.shared_w[(int64_t)m * a.n_shared + (g - a.E_routed)];
+      } else {
+        out = a.rslot[off_e + m];
+        gw = a.rgw[off_e + m];
+      }
+      if constexpr (INT && !GSC) sc = ascale[src];
+    } else {
+      src = m;
+      out = m;
+      if constexpr (INT && !GSC) sc = ascale[m];
+    }
+  }
+  float wsv = 0.f;
+  if constexpr (NAR) {
+    static_assert(NL * BN <= kThreads, "one channel scale per thread");
+    if constexpr (INT && !GSC) {
+      const int l = tid / BN, n = ch0 + tid % BN;
+      if (tid < NL * BN && n < N) wsv = lins[l]->wscale[n];
+    }
+    // the first weights follow the row data at once and land while the rows
+    // are looked up and staged (one memory round trip less per item)
+    asm volatile("" ::: "memory");
+    load_first();
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  if (tid < BM) {
+    sm.rowsrc[tid] = src;
+    sm.rowout[tid] = m0 < m_g ? out : -1;
+    sm.rowgw[tid] = gw;
+    sm.rowscale[tid] = sc;
+  }
+  if constexpr (INT && !GSC && NAR) {
+    if (tid < NL * BN) sm.wsc[tid] = wsv;
+  } else if constexpr (INT && !GSC) {  // the channels' weight scales, for the epilogue
+    for (int i = tid; i < NL * BN; i += kThreads) {
+      const int l = i / BN, c = i - l * BN;
+      const int n = ch0 + c;
+      sm.wsc[i] = n < N ? lins[l]->wscale[n] : 0.f;
+    }
+  }
+  const int64_t row_bytes = MX ? (int64_t)K / 2 : (int64_t)K * (INT ? 1 : 2);
+  if (tid == 0) sm.spec = spec;
+  if constexpr (NAR) lds_barrier();  // (leaves the weights in flight)
+  else __syncthreads();
+  // the tile after this one, claimed ahead: its entry comes into LDS now (every
+  // thread has read this tile's entry before the barrier above)
+  if constexpr (NAR) {
+    if (tid == 0) item_entry<true>(tile_queue(a, PHASE == kPhaseRaw ? 0 : PHASE), sm, spec);
+  } else {
+    if (tid == 0 && spec >= 0) claim_from<true>(tile_queue(a, PHASE == kPhaseRaw ? 0 : PHASE), sm, spec);
+  }
+  StageOffs<RB, BM> soffs;
+  stage_offsets<RB, BM>(soffs, sm, row_bytes, wave, lane);
+  // row sums of the tile's activation rows per k block (bias-dequantized
+  // kinds, bf16): x rows in the gate|up phase, h rows in the down phase
+  const float* rsbase = nullptr;
+  uint32_t rsoff = 0;
+  if constexpr (RSLOAD) {
+    // row sums (bias-dequantized kinds), activation group scales (w4a4-g128)
+    // or the four E8M0 bytes of a row's k block (mxfp4)
+    if constexpr (MX)
+      rsbase = reinterpret_cast<const float*>(PHASE == 1 ? (shared ? a.hsmx_shared : a.hsmx) : a.xsmx);
+    else if constexpr (GSC) rsbase = PHASE == 1 ? (shared ? a.hsg_shared : a.hsg) : a.xs4g;
+    else rsbase = PHASE == 1 ? (shared ? a.rsh_shared : a.rsh) : a.rsx;
+    const int r = wave * 64 + lane;
+    rsoff = (uint32_t)sm.rowsrc[r < BM ? r : 0] * (uint32_t)kblocks * 4u;
+  }
+
+  // ---- accumulators
+  AccT acc[NL][NF][MF];
+#pragma unroll
+  for (int l = 0; l < NL; ++l)
+#pragma unroll
+    for (int nf = 0; nf < NF; ++nf)
+#pragma unroll
+      for (int mf = 0; mf < MF; ++mf) acc[l][nf][mf] = AccT{0, 0, 0, 0};
+
   // Vector-memory loads issued after the activation stage (and its row sums) of
   // the next k block,
   // at least: one per fragment and step (streamed), one per fragment (group
@@ -714,19 +829,19 @@ __device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const G
   // (weight-only).  Waiting for
   // this many leaves the weight prefetch in flight across the barrier.
   constexpr int kLoadsAfterStage =
-      NL * NF * (streamed<KD>() ? J : ((KD == K_W8A8 || KD == K_F8A8 || KD == K_W4A4F6) ? 2 : 1)) + (GMETA ? NL * NF : 0);
+      NL * NF * (streamed<KD, NAR>() ? J : (KD == K_W3G && !NAR ? 1 : raw_loads<KD>())) + (GMETA ? NL * NF : 0);
 
   stage_load<RB, BM>(sm, 0, abase, soffs, kb0, wave);
-  if constexpr (RSLOAD) rowsum_load<BM, MX>(sm, 0, rsbase, rsoff, kb0, wave);
-  if constexpr (KBI == 2) {
-    if (kb0 + 1 < kb1) {
-      stage_load<RB, BM>(sm, 0, abase, soffs, kb0 + 1, wave, 1);
-      if constexpr (RSLOAD) rowsum_load<BM, MX>(sm, 0, rsbase, rsoff, kb0 + 1, wave, 1);
+  if constexpr (RSLOAD) rowsum_load<BM, MX || NAR, RSS>(sm, 0, rsbase, rsoff, kb0, wave);
+#pragma unroll
+  for (int sb = 1; sb < KBI; ++sb) {
+    if (kb0 + sb < kb1) {
+      stage_load<RB, BM>(sm, 0, abase, soffs, kb0 + sb, wave, sb);
+      if constexpr (RSLOAD) rowsum_load<BM, MX || NAR, RSS>(sm, 0, rsbase, rsoff, kb0 + sb, wave, sb);
     }
   }
-  load_group(std::integral_constant<int, 0>{}, kb0, false);
-  if constexpr (KBI == 2) load_group(std::integral_constant<int, 1>{}, kb0 + 1, kb0 + 1 >= kb1);
-  if constexpr (streamed<KD>()) {
+  if constexpr (!NAR) load_first();
+  if constexpr (streamed<KD, NAR>()) {
 #pragma unroll
     for (int j = 0; j < J; ++j) load_steps(kb0, false, j);
   }
@@ -740,7 +855,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const G
     // for here, before the stage loads below go out: the compiler does not
     // count those direct loads, so a wait it placed after them for an older
     // load would wait for them too (vector-memory loads complete in order).
-    if constexpr (!streamed<KD>()) {
+    if constexpr (!streamed<KD, NAR>()) {
 #pragma unroll
       for (int l = 0; l < NL; ++l)
 #pragma unroll
@@ -753,7 +868,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const G
     for (int sb = 0; sb < KBI; ++sb) {
       if (kb + KBI + sb < kb1) {
         stage_load<RB, BM>(sm, cur ^ 1, abase, soffs, kb + KBI + sb, wave, sb);
-        if constexpr (RSLOAD) rowsum_load<BM, MX>(sm, cur ^ 1, rsbase, rsoff, kb + KBI + sb, wave, sb);
+        if constexpr (RSLOAD) rowsum_load<BM, MX || NAR, RSS>(sm, cur ^ 1, rsbase, rsoff, kb + KBI + sb, wave, sb);
       }
     }
     // every weight load below is issued after the stage (see wait_vmem)
@@ -762,11 +877,11 @@ __device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const G
     // one k block (kbs = kb + SL) of the step; an inactive block (the second
     // one past the last k block) issues only what every path through the step
     // issues, so the compiler's wait counts need no drain where paths join
-    auto kstep = [&](auto S, bool active) {
+    auto kstep = [&](auto S, bool active) __attribute__((always_inline)) {
     constexpr int SL = decltype(S)::value;
     const int kbs = kb + SL;
     const int ra = SL * BM;   // first staged row of this k block
-    const int rs0 = SL * 64;  // its per-row values
+    const int rs0 = SL * RSS;  // its per-row values
     if (active) {
     Raw<KD> rw[NL][NF];
     uint32_t bz[NL][NF];
@@ -799,7 +914,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const G
 #pragma unroll
           for (int mf = 0; mf < MF; ++mf) {
             f32x4 cr = {0, 0, 0, 0};
-            if constexpr (RSUM) cr = *reinterpret_cast<const f32x4*>(&sm.rsum[cur][rs0 + mf * 16 + 4 * q]) * (-CB);
+            if constexpr (RSUM && !NAR) cr = *reinterpret_cast<const f32x4*>(&sm.rsum[cur][rs0 + mf * 16 + 4 * q]) * (-CB);
 #pragma unroll
             for (int i = 0; i < 4; ++i) acc[l][nf][mf][i] = __builtin_fmaf(acc[l][nf][mf][i], r, cr[i]);
           }
@@ -934,19 +1049,31 @@ __device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const G
           }
       }
     } else {
+    // row sums of this k block's activations (C layout: the rows of acc[.][.][mf])
+    constexpr int NMM = NL * NF + (RSMMA ? 1 : 0);  // MFMAs per activation fragment
+    f32x4 rsa[RSMMA ? MF : 1];
+    if constexpr (RSMMA) {
+#pragma unroll
+      for (int mf = 0; mf < MF; ++mf) rsa[mf] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
 #pragma unroll
     for (int j = 0; j < J; ++j) {
-      auto wop = [&](int l, int nf) -> OpT {
-        const u32x4 sv = streamed<KD>() ? st[j][l][nf] : u32x4{0u, 0u, 0u, 0u};
+      auto wop = [&](int l, int nf) __attribute__((always_inline)) -> OpT {
+        u32x4 sv = streamed<KD, NAR>() ? st[j][l][nf] : u32x4{0u, 0u, 0u, 0u};
+        if constexpr (NAR && KD == K_W16) sv = wr[l][nf].d[j];
+        if constexpr (NAR && KD == K_W8G) sv = u32x4{wr[l][nf].d[j >> 1][2 * (j & 1)], wr[l][nf].d[j >> 1][2 * (j & 1) + 1], 0u, 0u};
         if constexpr (INT) return wfrag8<KD>(wr[l][nf], sv, j);
         else return wfrag16<KD, ACT>(wr[l][nf], sv, j, bz[l][nf], zf[l][nf]);
       };
-      auto aop = [&](int mf) -> OpT {
+      auto aop = [&](int mf) __attribute__((always_inline)) -> OpT {
         return __builtin_bit_cast(OpT, act_frag<RB>(sm, cur, ra + mf * 16 + li, 4 * j + q));
       };
-      auto mma = [&](const OpT& af, const OpT& wf, AccT c) -> AccT {
+      auto mma = [&](const OpT& af, const OpT& wf, AccT c) __attribute__((always_inline)) -> AccT {
         if constexpr (INT) return __builtin_amdgcn_mfma_i32_16x16x64_i8(af, wf, c, 0, 0, 0);
         else return mfma16<ACT>(af, wf, c);
+      };
+      auto rowsums = [&](int mf, const OpT& af) __attribute__((always_inline)) {
+        if constexpr (RSMMA) rsa[mf] = mfma16<ACT>(af, u32x4{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u}, rsa[mf]);
       };
       if constexpr (HOLD_W) {
         OpT wf[NL][NF];
@@ -958,11 +1085,13 @@ __device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const G
 #pragma unroll
         for (int mf = 0; mf < MF; ++mf) af[mf] = aop(mf);
 #pragma unroll
-        for (int mf = 0; mf < MF; ++mf)
+        for (int mf = 0; mf < MF; ++mf) {
+          rowsums(mf, af[mf]);
 #pragma unroll
           for (int l = 0; l < NL; ++l)
 #pragma unroll
             for (int nf = 0; nf < NF; ++nf) acc[l][nf][mf] = mma(af[mf], wf[l][nf], acc[l][nf][mf]);
+        }
         // Software pipeline of the activation fragments: two LDS reads ahead,
         // then the MFMAs of one fragment and the read of the fragment two
         // places further, so an MFMA group never waits for a read issued just
@@ -972,14 +1101,17 @@ __device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const G
           __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
 #pragma unroll
           for (int mf = 0; mf < MF; ++mf) {
-            __builtin_amdgcn_sched_group_barrier(0x008, NL * NF, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, NMM, 0);
             if (mf + 2 < MF) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
           }
         }
       } else {
         OpT af[MF];
 #pragma unroll
-        for (int mf = 0; mf < MF; ++mf) af[mf] = aop(mf);
+        for (int mf = 0; mf < MF; ++mf) {
+          af[mf] = aop(mf);
+          rowsums(mf, af[mf]);
+        }
 #pragma unroll
         for (int l = 0; l < NL; ++l)
 #pragma unroll
@@ -989,11 +1121,21 @@ __device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const G
             for (int mf = 0; mf < MF; ++mf) acc[l][nf][mf] = mma(af[mf], wf, acc[l][nf][mf]);
           }
       }
-      if constexpr (streamed<KD>()) {
+      if constexpr (streamed<KD, NAR>()) {
         // step j's registers are free: refill them with step j of the next block
         load_steps(kb + 1, !more, j);
         __builtin_amdgcn_sched_barrier(0);
       }
+    }
+    if constexpr (RSMMA) {  // the bias times the row sums leaves the sum here
+#pragma unroll
+      for (int mf = 0; mf < MF; ++mf)
+#pragma unroll
+        for (int l = 0; l < NL; ++l)
+#pragma unroll
+          for (int nf = 0; nf < NF; ++nf)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[l][nf][mf][i] = __builtin_fmaf(rsa[mf][i], -CB, acc[l][nf][mf][i]);
     }
     if constexpr (HOLD_W && INT) {
       // the activation fragments of all MFMA steps of the k block in one
@@ -1009,14 +1151,18 @@ __device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const G
     }
     }
     }  // active
-    if constexpr (KBI == 2) {
+    if constexpr (KBI > 1) {
       // this slot's registers are free: prefetch its block of the next step
       load_group(S, kbs + KBI, kbs + KBI >= kb1);
       __builtin_amdgcn_sched_barrier(0);
     }
     };  // kstep
     kstep(std::integral_constant<int, 0>{}, true);
-    if constexpr (KBI == 2) kstep(std::integral_constant<int, 1>{}, kb + 1 < kb1);
+    if constexpr (KBI > 1) kstep(std::integral_constant<int, 1>{}, kb + 1 < kb1);
+    if constexpr (KBI > 2) {
+      kstep(std::integral_constant<int, 2>{}, kb + 2 < kb1);
+      kstep(std::integral_constant<int, 3>{}, kb + 3 < kb1);
+    }
     // The next stages have landed once no more than the weight prefetch is
     // outstanding (vector-memory loads complete in issue order; when more
     // steps follow, every k block of this one issued its prefetch).
@@ -1032,7 +1178,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const G
   // keeps the claim's pending loads out of the loop: the compiler would
   // otherwise drain every outstanding load, the prefetch of the next k blocks
   // included, at the top of each step.
-  if (tid == 0 && sm.spec < 0) claim_next<true>(tile_queue(a, PHASE == kPhaseRaw ? 0 : PHASE), sm);
+  if (!NAR && tid == 0 && sm.spec < 0) claim_next<true>(tile_queue(a, PHASE == kPhaseRaw ? 0 : PHASE), sm);
 
   // ---- split-K: partial sums of this slice; the last slice to arrive adds
   // all slices' partials in slice order and runs the epilogue
@@ -1053,9 +1199,13 @@ __device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const G
     const PlanLayout PL = plan_layout(a.G, a.qcap, a.fcap);
     const int32_t* rec = a.plan + PL.rec + ((int64_t)pidx * a.G + g) * PF_N;
     const int otile = mt * ntr + nt;
-    int32_t* cnt = a.plan + PL.cnt + (int64_t)pidx * kSplitExtra + rec[PF_CBASE] + otile;
-    float* part = a.partial + rec[PF_PBASE] + (int64_t)otile * split * AREA;
-    auto at_of = [&](int l, int nf, int mf) {  // this lane's 16 bytes of a fragment
+    // (a planned tile claimed in NSUB items has NSUB counters, and its
+    // partial sums hold the items' areas side by side within a slice)
+    constexpr int NSUB = NAR ? 1 << kNarrowLog : 1;
+    constexpr int SSTRIDE = AREA * NSUB;  // floats from one slice of an item to the next
+    int32_t* cnt = a.plan + PL.cnt + (int64_t)pidx * kSplitExtra + (rec[PF_CBASE] + otile) * NSUB + (NAR ? sub : 0);
+    float* part = a.partial + rec[PF_PBASE] + (int64_t)otile * split * SSTRIDE + (NAR ? sub : 0) * AREA;
+    auto at_of = [&](int l, int nf, int mf) __attribute__((always_inline)) {  // this lane's 16 bytes of a fragment
       return ((((wave * NL + l) * NF + nf) * MF + mf) * 64 + lane) * 4;
     };
     // The partials are stored and loaded with device-scope coherent accesses
@@ -1068,7 +1218,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const G
       for (int nf = 0; nf < NF; ++nf)
 #pragma unroll
         for (int mf = 0; mf < MF; ++mf)
-          store_coherent(part + (int64_t)slice * AREA + at_of(l, nf, mf), __builtin_bit_cast(u32x4, acc[l][nf][mf]));
+          store_coherent(part + (int64_t)slice * SSTRIDE + at_of(l, nf, mf), __builtin_bit_cast(u32x4, acc[l][nf][mf]));
     wait_vmem<0>();  // this wavefront's partials are written
     __syncthreads();
     if (tid == 0) sm.last = atomicAdd(cnt, 1) == split - 1;
@@ -1077,24 +1227,26 @@ __device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const G
     if (finish) {
       // every slice (this one included) is read back and summed in slice
       // order, so the result does not depend on which slice finished last.
-      if constexpr (PHASE == 1) {
+      if constexpr (PHASE == 1 || NAR) {
         // Down tiles (the deep reductions that get many slices) read through
-        // the stage buffers (free after the k loop), 16 KB per wavefront: a
+        // the stage buffers (free after the k loop), WLDS bytes per wavefront: a
         // unit is one slice of one fragment column (MF loads of 1 KB, straight
         // into LDS), and QU units are in flight while the oldest is added from
         // LDS, so that their memory round trips overlap.  (In the gate|up
         // kernels the extra code measured 0.5% slower on unsliced tiles.)
-        constexpr int QU = (16 / MF) < 4 ? (16 / MF) : 4;
-        const uint32_t ldsw = (uint32_t)reinterpret_cast<uintptr_t>((lds_ptr_t)sm.act[0]) + wave * 16384;
+        constexpr int WLDS = 2 * STAGE / 4;
+        constexpr int QMAX = NAR ? 8 : 4;
+        constexpr int QU = (WLDS / 1024 / MF) < QMAX ? (WLDS / 1024 / MF) : QMAX;
+        const uint32_t ldsw = lds_base(sm) + (uint32_t)(offsetof(Smem<NAR>, act) + wave * WLDS);
         const uint8_t* pbase = reinterpret_cast<const uint8_t*>(part);
         const int nunits = NL * NF * split;
-        auto issue = [&](int u) {  // unit u = (column, slice) into slot u % QU
+        auto issue = [&](int u) __attribute__((always_inline)) {  // unit u = (column, slice) into slot u % QU
           const int col = u / split, sl = u - col * split;
           const int l = col / NF, nf = col - l * NF;
           const uint32_t slot = ldsw + (uint32_t)((u % QU) * MF) * 1024u;
 #pragma unroll
           for (int mf = 0; mf < MF; ++mf)
-            lds_dma16_coherent(pbase, (uint32_t)(((int64_t)sl * AREA + at_of(l, nf, mf)) * 4),
+            lds_dma16_coherent(pbase, (uint32_t)(((int64_t)sl * SSTRIDE + at_of(l, nf, mf)) * 4),
                                __builtin_amdgcn_readfirstlane(slot + mf * 1024u));
         };
         for (int u = 0; u < QU && u < nunits; ++u) issue(u);
@@ -1105,11 +1257,15 @@ __device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const G
             for (int sl = 0; sl < split; ++sl) {
               const int u = (l * NF + nf) * split + sl;
               const int newer = (u + QU < nunits ? u + QU : nunits) - u - 1;  // units issued after u
-              if (newer >= 3) wait_vmem<3 * MF>();
+              if (QU > 7 && newer == 7) wait_vmem<7 * (QU > 7 ? MF : 0)>();
+              else if (QU > 6 && newer == 6) wait_vmem<6 * (QU > 6 ? MF : 0)>();
+              else if (QU > 5 && newer == 5) wait_vmem<5 * (QU > 5 ? MF : 0)>();
+              else if (QU > 4 && newer == 4) wait_vmem<4 * (QU > 4 ? MF : 0)>();
+              else if (newer >= 3) wait_vmem<3 * MF>();
               else if (newer == 2) wait_vmem<2 * MF>();
               else if (newer == 1) wait_vmem<MF>();
               else wait_vmem<0>();
-              const uint8_t* src = reinterpret_cast<const uint8_t*>(sm.act[0]) + wave * 16384 + (u % QU) * MF * 1024;
+              const uint8_t* src = reinterpret_cast<const uint8_t*>(sm.act[0]) + wave * WLDS + (u % QU) * MF * 1024;
 #pragma unroll
               for (int mf = 0; mf < MF; ++mf) {
                 const u32x4 v = *reinterpret_cast<const u32x4*>(src + mf * 1024 + lane * 16);
@@ -1129,7 +1285,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const G
             for (int sl = 0; sl < split; ++sl) {
               u32x4 v[MF];
 #pragma unroll
-              for (int mf = 0; mf < MF; ++mf) v[mf] = load_coherent(part + (int64_t)sl * AREA + at_of(l, nf, mf));
+              for (int mf = 0; mf < MF; ++mf) v[mf] = load_coherent(part + (int64_t)sl * SSTRIDE + at_of(l, nf, mf));
               wait_loaded<MF>(v);
 #pragma unroll
               for (int mf = 0; mf < MF; ++mf)
@@ -1148,12 +1304,12 @@ __device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const G
   // writes the row sums of its h values per 128-wide block, which the down
   // phase subtracts (the tile's channels are whole blocks: BN is 128 or 256)
   float* rsh_out = nullptr;
-  if constexpr (PHASE == 0 && ACT == MXMOE_BF16) {
+  if constexpr (PHASE == 0 && ACT == MXMOE_BF16 && !NAR) {
     // (the kind is read as a wave-uniform value: the branch around the barrier
     // below must not look divergent to the compiler)
     if (kind_is_magic(__builtin_amdgcn_readfirstlane(ex->lin[2].kind))) rsh_out = shared ? a.rsh_shared : a.rsh;
   }
-  auto epilogue = [&](auto guard) {
+  auto epilogue = [&](auto guard) __attribute__((always_inline)) {
     constexpr bool GUARD = decltype(guard)::value;
     float cs[NL][NF];
 #pragma unroll
@@ -1165,7 +1321,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const G
         if constexpr (WONLY) cs[l][nf] = s_prev[l][nf];
       }
     // value of accumulator (l, nf, mf, i) after the scheme's scales
-    auto outv = [&](int l, int nf, int mf, int i, const f32x4& rs) -> float {
+    auto outv = [&](int l, int nf, int mf, int i, const f32x4& rs) __attribute__((always_inline)) -> float {
       if constexpr (F8 || F6) {
         return (acc[l][nf][mf][i] * rs[i]) * cs[l][nf];
       } else if constexpr (INT && !GSC) {
@@ -1181,7 +1337,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const G
       // idle stage buffers), then out in 16-byte row pieces; the h row sums of
       // a bias-dequantized down projection are added from the same LDS rows
       constexpr int HP = BN + 8;  // row pitch in elements (16-byte pad: reads of 16 rows hit distinct banks)
-      static_assert(BM * HP * 2 <= 2 * STAGE_BYTES, "h tile fits the stage buffers");
+      static_assert(BM * HP * 2 <= 2 * STAGE, "h tile fits the stage buffers");
       uint16_t* hl = reinterpret_cast<uint16_t*>(&sm.act[0][0]);
       // (channels past N are computed too, without a branch per fragment,
       // and never stored; each fragment's four values go through the SiLU in
@@ -1210,14 +1366,14 @@ __device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const G
       wait_vmem<0>();  // the next tile's entry has landed
       lds_barrier();
       constexpr int CH = BN / 8;  // 16-byte pieces of a tile row
-      int nch = (N - nt * BN) / 8;
+      int nch = (N - ch0) / 8;
       nch = nch > CH ? CH : nch;
       uint16_t* hout = reinterpret_cast<uint16_t*>(shared ? a.h_shared : a.h);
       for (int idx = tid; idx < BM * CH; idx += kThreads) {
         const int r = idx / CH, c = idx % CH;
         const int ro = sm.rowout[r];
         if (ro >= 0 && c < nch)
-          *reinterpret_cast<u32x4*>(hout + (int64_t)ro * N + nt * BN + 8 * c) =
+          *reinterpret_cast<u32x4*>(hout + (int64_t)ro * N + ch0 + 8 * c) =
               *reinterpret_cast<const u32x4*>(hl + r * HP + 8 * c);
       }
       if (rsh_out) {  // one thread per (row, 128-wide block): its 128 bf16 values in order
@@ -1225,7 +1381,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const G
         const int nkb = N / 128;
         for (int idx = tid; idx < BM * KBT; idx += kThreads) {
           const int r = idx % BM, j = idx / BM;
-          const int kbg = nt * KBT + j;
+          const int kbg = ch0 / 128 + j;
           const int ro = sm.rowout[r];
           if (ro < 0 || kbg >= nkb) continue;
           float t = 0.f;
@@ -1249,11 +1405,11 @@ __device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const G
       // to the activation dtype (a.slot16, the default), or kept in fp32.
       if (a.slot16) {
         constexpr int HP = BN + 8;                  // row pitch in elements (16-byte pad against bank conflicts)
-        constexpr int RP = (BM >= 64 && 64 * HP * 2 <= 2 * STAGE_BYTES) ? 64 : BM;  // rows per pass
-        static_assert(RP * HP * 2 <= 2 * STAGE_BYTES, "slot rows fit the stage buffers");
+        constexpr int RP = (BM >= 64 && 64 * HP * 2 <= 2 * STAGE) ? 64 : BM;  // rows per pass
+        static_assert(RP * HP * 2 <= 2 * STAGE, "slot rows fit the stage buffers");
         uint16_t* hl = reinterpret_cast<uint16_t*>(&sm.act[0][0]);
         constexpr int CH = BN / 8;                  // 16-byte pieces of a tile row
-        int nch = (N - nt * BN) / 8;
+        int nch = (N - ch0) / 8;
         nch = nch > CH ? CH : nch;
         uint16_t* sout = reinterpret_cast<uint16_t*>(a.slots);
 #pragma unroll
@@ -1284,18 +1440,18 @@ __device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const G
             const int r = idx / CH, c = idx % CH;
             const int ro = sm.rowout[pass * RP + r];
             if (ro >= 0 && c < nch)
-              *reinterpret_cast<u32x4*>(sout + (int64_t)ro * N + nt * BN + 8 * c) =
+              *reinterpret_cast<u32x4*>(sout + (int64_t)ro * N + ch0 + 8 * c) =
                   *reinterpret_cast<const u32x4*>(hl + r * HP + 8 * c);
           }
           lds_barrier();
         }
       } else {
       constexpr int FP = BN + 4;                  // row pitch in floats (16-byte pad against bank conflicts)
-      constexpr int RP = (BM >= 32 && 32 * FP * 4 <= 2 * STAGE_BYTES) ? 32 : 16;  // rows per pass
-      static_assert(RP * FP * 4 <= 2 * STAGE_BYTES, "slot rows fit the stage buffers");
+      constexpr int RP = (BM >= 32 && 32 * FP * 4 <= 2 * STAGE) ? 32 : 16;  // rows per pass
+      static_assert(RP * FP * 4 <= 2 * STAGE, "slot rows fit the stage buffers");
       float* fl = reinterpret_cast<float*>(&sm.act[0][0]);
       constexpr int CH = BN / 4;                  // 16-byte pieces of a tile row
-      int nch = (N - nt * BN) / 4;
+      int nch = (N - ch0) / 4;
       nch = nch > CH ? CH : nch;
 #pragma unroll
       for (int pass = 0; pass < BM / RP; ++pass) {
@@ -1318,7 +1474,7 @@ __device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const G
           const int r = idx / CH, c = idx % CH;
           const int ro = sm.rowout[pass * RP + r];
           if (ro >= 0 && c < nch)
-            *reinterpret_cast<u32x4*>(reinterpret_cast<float*>(a.slots) + (int64_t)ro * N + nt * BN + 4 * c) =
+            *reinterpret_cast<u32x4*>(reinterpret_cast<float*>(a.slots) + (int64_t)ro * N + ch0 + 4 * c) =
                 *reinterpret_cast<const u32x4*>(fl + r * FP + 4 * c);
         }
         lds_barrier();
@@ -1360,34 +1516,38 @@ __device__ __attribute__((always_inline)) inline void run_tile(Smem& sm, const G
   __syncthreads();  // the next tile rewrites rowsrc and the stages
 }
 
-template <int ACT, int PHASE, int CFG>
-__device__ __attribute__((always_inline)) inline void dispatch_kind(Smem& sm, const GemmArgs& a, const DevExpert* ex, int g, int m_g, int mt, int nt,
-                                     int off_e, int kd, int split) {
+template <int ACT, int PHASE, int CFG, bool NAR>
+MXMOE_INL void dispatch_kind(Smem<NAR>& sm, const GemmArgs& a, const DevExpert* ex, int g, int m_g, int mt, int nt,
+                                     int off_e, int kd, int split, int pcfg, int sub) {
+  // kinds planned in at most 64-row tiles have no 128-row form (narrow: no 64-row form)
+  constexpr bool TOP = CFG == (NAR ? CFG_M : CFG_L);
+#define MXMOE_RUN(KD) run_tile<KD, ACT, CFG, PHASE, NAR>(sm, a, ex, g, m_g, mt, nt, off_e, split, pcfg, sub)
   switch (kd) {
-    case K_W16: run_tile<K_W16, ACT, CFG, PHASE>(sm, a, ex, g, m_g, mt, nt, off_e, split); break;
-    case K_W8A8: run_tile<K_W8A8, ACT, CFG, PHASE>(sm, a, ex, g, m_g, mt, nt, off_e, split); break;
+    case K_W16: MXMOE_RUN(K_W16); break;
+    case K_W8A8: MXMOE_RUN(K_W8A8); break;
     case K_F8A8:  // planned in 128-row tiles in the down phase only
-      if constexpr (CFG != CFG_L || PHASE == 1) run_tile<K_F8A8, ACT, CFG, PHASE>(sm, a, ex, g, m_g, mt, nt, off_e, split);
+      if constexpr (!TOP || PHASE == 1) MXMOE_RUN(K_F8A8);
       break;
-    case K_W4A4: run_tile<K_W4A4, ACT, CFG, PHASE>(sm, a, ex, g, m_g, mt, nt, off_e, split); break;
-    case K_W4A4F6: run_tile<K_W4A4F6, ACT, CFG, PHASE>(sm, a, ex, g, m_g, mt, nt, off_e, split); break;
-    case K_W2G: run_tile<K_W2G, ACT, CFG, PHASE>(sm, a, ex, g, m_g, mt, nt, off_e, split); break;
-    case K_W3G: run_tile<K_W3G, ACT, CFG, PHASE>(sm, a, ex, g, m_g, mt, nt, off_e, split); break;
-    case K_W4G: run_tile<K_W4G, ACT, CFG, PHASE>(sm, a, ex, g, m_g, mt, nt, off_e, split); break;
-    case K_W8G: run_tile<K_W8G, ACT, CFG, PHASE>(sm, a, ex, g, m_g, mt, nt, off_e, split); break;
+    case K_W4A4: MXMOE_RUN(K_W4A4); break;
+    case K_W4A4F6: MXMOE_RUN(K_W4A4F6); break;
+    case K_W2G: MXMOE_RUN(K_W2G); break;
+    case K_W3G: MXMOE_RUN(K_W3G); break;
+    case K_W4G: MXMOE_RUN(K_W4G); break;
+    case K_W8G: MXMOE_RUN(K_W8G); break;
     case K_W4A4G:  // never planned in 128-row tiles
-      if constexpr (CFG != CFG_L) run_tile<K_W4A4G, ACT, CFG, PHASE>(sm, a, ex, g, m_g, mt, nt, off_e, split);
+      if constexpr (!TOP) MXMOE_RUN(K_W4A4G);
       break;
     case K_MXFP4:  // never planned in 128-row tiles
-      if constexpr (CFG != CFG_L) run_tile<K_MXFP4, ACT, CFG, PHASE>(sm, a, ex, g, m_g, mt, nt, off_e, split);
+      if constexpr (!TOP) MXMOE_RUN(K_MXFP4);
       break;
     default: break;
   }
+#undef MXMOE_RUN
 }
 
 template <int ACT, int PHASE>
 __global__ void __launch_bounds__(kThreads, 2) group_gemm_kernel(GemmArgs a) {
-  __shared__ Smem sm;
+  __shared__ Smem<false> sm;
   {
     const TileQueue Q = tile_queue(a, PHASE == kPhaseRaw ? 0 : PHASE);
     if (threadIdx.x < kXcd) sm.qtotal[threadIdx.x] = min(Q.ctr[threadIdx.x * 4 + 1], a.fcap);
@@ -1418,10 +1578,61 @@ __global__ void __launch_bounds__(kThreads, 2) group_gemm_kernel(GemmArgs a) {
     // (every thread has read the entry: run_tile passes a barrier before
     // thread 0 claims the next tile into it)
     switch (cfg) {
-      case CFG_S: dispatch_kind<ACT, PHASE, CFG_S>(sm, a, ex, g, m_g, mt, nt, off_e, kd, split); break;
-      case CFG_T: dispatch_kind<ACT, PHASE, CFG_T>(sm, a, ex, g, m_g, mt, nt, off_e, kd, split); break;
-      case CFG_M: dispatch_kind<ACT, PHASE, CFG_M>(sm, a, ex, g, m_g, mt, nt, off_e, kd, split); break;
-      default: dispatch_kind<ACT, PHASE, CFG_L>(sm, a, ex, g, m_g, mt, nt, off_e, kd, split); break;
+      case CFG_S: dispatch_kind<ACT, PHASE, CFG_S, false>(sm, a, ex, g, m_g, mt, nt, off_e, kd, split, cfg, 0); break;
+      case CFG_T: dispatch_kind<ACT, PHASE, CFG_T, false>(sm, a, ex, g, m_g, mt, nt, off_e, kd, split, cfg, 0); break;
+      case CFG_M: dispatch_kind<ACT, PHASE, CFG_M, false>(sm, a, ex, g, m_g, mt, nt, off_e, kd, split, cfg, 0); break;
+      default: dispatch_kind<ACT, PHASE, CFG_L, false>(sm, a, ex, g, m_g, mt, nt, off_e, kd, split, cfg, 0); break;
+    }
+  }
+}
+
+// The narrow form: items spread evenly over the resident workgroups.
+template <int ACT, int PHASE>
+__global__ void __launch_bounds__(kThreads, kNarrowWgs) group_gemm_narrow_kernel(GemmArgs a) {
+  __shared__ Smem<true> sm;
+  {
+    const TileQueue Q = tile_queue(a, PHASE == kPhaseRaw ? 0 : PHASE);
+    if (threadIdx.x < kXcd) sm.qtotal[threadIdx.x] = min(Q.ctr[threadIdx.x * 4 + 1], a.fcap);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      int n = 0;
+      for (int x = 0; x < kXcd; ++x) n += sm.qtotal[x];
+      sm.qi = n << kNarrowLog;
+      item_entry<false>(Q, sm, blockIdx.x);
+    }
+    __syncthreads();
+  }
+  for (;;) {
+    const int w0 = __builtin_amdgcn_readfirstlane(sm.entry.x);
+    if (w0 < 0) break;
+    const int w1 = __builtin_amdgcn_readfirstlane(sm.entry.y);
+    const int off_e = __builtin_amdgcn_readfirstlane(sm.entry.z);
+    const int m_g = __builtin_amdgcn_readfirstlane(sm.entry.w);
+    const int sub = __builtin_amdgcn_readfirstlane(sm.cur_idx) & ((1 << kNarrowLog) - 1);
+    const int g = w0 & 0xFFFF, cfg = (w0 >> 16) & 15, kd = (w0 >> 20) & 15, split = ((w0 >> 24) & 7) + 1;
+    const int mt = w1 & 0xFFFF, nt = w1 >> 16;
+    const DevExpert* ex = PHASE == kPhaseRaw ? nullptr : a.experts + g;
+    const int N = PHASE == kPhaseRaw ? a.raw_lin.n : ex->lin[PHASE == 0 ? 0 : 2].n;
+    constexpr int BN = 64 * narrow_nf(PHASE == 0 ? 0 : 1);
+    const int bnw = narrow_bn(cfg, BN);
+    int ct = nt;  // channel tile, without the slice
+    if (split > 1) ct -= nt / ((N + bnw - 1) / bnw) * ((N + bnw - 1) / bnw);
+    const int bm = cfg == CFG_S ? 16 : (cfg == CFG_L ? 64 : 32);
+    // an item past the group's rows or channels: nothing to do
+    if (narrow_row0(cfg, mt, sub, bm) >= m_g || narrow_ch0(cfg, ct, sub, BN) >= N) {
+      __syncthreads();  // every thread has read the entry
+      if (threadIdx.x == 0) {
+        const TileQueue Q = tile_queue(a, PHASE == kPhaseRaw ? 0 : PHASE);
+        item_entry<false>(Q, sm, claim_item(Q, sm));
+      }
+      __syncthreads();
+      continue;
+    }
+    switch (cfg) {
+      case CFG_S: dispatch_kind<ACT, PHASE, CFG_S, true>(sm, a, ex, g, m_g, mt, nt, off_e, kd, split, cfg, sub); break;
+      case CFG_T:
+      case CFG_M: dispatch_kind<ACT, PHASE, CFG_T, true>(sm, a, ex, g, m_g, mt, nt, off_e, kd, split, cfg, sub); break;
+      default: dispatch_kind<ACT, PHASE, CFG_M, true>(sm, a, ex, g, m_g, mt, nt, off_e, kd, split, cfg, sub); break;
     }
   }
 }
@@ -1429,10 +1640,10 @@ __global__ void __launch_bounds__(kThreads, 2) group_gemm_kernel(GemmArgs a) {
 }  // namespace
 
 // Per-(activation dtype, phase) launchers, one translation unit each.
-#define MXMOE_GG_LAUNCHER(NAME, ACT, PHASE)                                                   \
-  hipError_t NAME(const GemmArgs& a, int grid, hipStream_t s) {                               \
-    hipLaunchKernelGGL((group_gemm_kernel<ACT, PHASE>), dim3(grid), dim3(kThreads), 0, s, a); \
-    return hipGetLastError();                                                                 \
+#define MXMOE_GG_LAUNCHER(NAME, KERNEL, ACT, PHASE)                                     \
+  hipError_t NAME(const GemmArgs& a, int grid, hipStream_t s) {                         \
+    hipLaunchKernelGGL((KERNEL<ACT, PHASE>), dim3(grid), dim3(kThreads), 0, s, a);      \
+    return hipGetLastError();                                                           \
   }
 
 hipError_t gg_bf16_p0(const GemmArgs& a, int grid, hipStream_t s);
@@ -1441,5 +1652,11 @@ hipError_t gg_bf16_raw(const GemmArgs& a, int grid, hipStream_t s);
 hipError_t gg_f16_p0(const GemmArgs& a, int grid, hipStream_t s);
 hipError_t gg_f16_p1(const GemmArgs& a, int grid, hipStream_t s);
 hipError_t gg_f16_raw(const GemmArgs& a, int grid, hipStream_t s);
+hipError_t gg_bf16_n0(const GemmArgs& a, int grid, hipStream_t s);
+hipError_t gg_bf16_n1(const GemmArgs& a, int grid, hipStream_t s);
+hipError_t gg_bf16_nraw(const GemmArgs& a, int grid, hipStream_t s);
+hipError_t gg_f16_n0(const GemmArgs& a, int grid, hipStream_t s);
+hipError_t gg_f16_n1(const GemmArgs& a, int grid, hipStream_t s);
+hipError_t gg_f16_nraw(const GemmArgs& a, int grid, hipStream_t s);
 
 }  // namespace mxmoe

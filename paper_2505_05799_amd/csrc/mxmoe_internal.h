@@ -268,6 +268,25 @@ struct WsLayout {
   int64_t pfloats;  // size of the partial buffer
 };
 
+// Launches that take the narrow form of the Group-GEMM, by an upper bound of
+// their tiles from the sizes: at most kNarrowFew tiles (they leave most of the
+// chip idle), or at most kNarrowTiles whose weights average kNarrowBytes a
+// tile (streaming them then outweighs the round trips, about 10 us, of the
+// four items a tile becomes).  Measured wide -> narrow, whole forward: 1 token
+// of the Qwen1.5-shaped block (88 tiles) 106 -> 65 us; 13 tokens of the
+// DeepSeek-V2-Lite-shaped one (737 tiles, 346 KB) 104 -> 85; Mixtral-shaped
+// with 16-bit weights, 40 tokens, 1230 -> 664; the 500-token DeepSeek-V2-Lite-
+// shaped block in 16 bits (1397 tiles, 528 KB) 390 -> 361.  On the other side:
+// Qwen1.5-shaped, 256 tokens, w4a4 (1056 tiles, 175 KB) 111 -> 120;
+// Mixtral-shaped, 206 tokens (1568 tiles, 188 KB) 467 -> 475; an mxfp4 linear
+// of 762 rows (564 tiles, 45 KB) 73 -> 75.
+// A narrow item has four arrival counters per sliced tile, which kSplitExtra /
+// 4 sliced tiles still fit.
+constexpr int64_t kNarrowFew = 512;
+constexpr int64_t kNarrowTiles = 2048;
+constexpr int64_t kNarrowBytes = 192 << 10;
+static_assert(4 * kNarrowTiles <= kSplitExtra, "arrival counters of narrow items");
+
 constexpr int kRouteChunk = 512;  // pairs per routing workgroup
 constexpr size_t kNone = (size_t)-1;
 
@@ -430,14 +449,15 @@ struct XPrep {
 // The plan prices tiles with the process-wide cost table (tile_costs_get).
 hipError_t launch_plan(const DevExpert* experts, int E, int G, int T, const int32_t* counts,
                        const int32_t* offsets, int raw_m, const DevLinear& raw_lin, const uint32_t* mask_words,
-                       int32_t* plan, int qcap, int fcap, int64_t pfloats, int32_t* down_qmax, int nwg,
+                       int32_t* plan, int qcap, int fcap, int64_t pfloats, int32_t* down_qmax, int nwg, bool narrow,
                        const XPrep& xp, hipStream_t s);
 // Process-wide tile cost table: the roofline default until a caller sets one;
 // set (nullptr restores the default) and get copy under a lock.
 void tile_costs_default(TileCosts* out);
 void tile_costs_set(const TileCosts* t);
 void tile_costs_get(TileCosts* out);
-hipError_t launch_group_gemm(const GemmArgs& a, int phase, int grid, hipStream_t s);
+// grid: workgroups of the wide form; narrow: the narrow form, on twice as many
+hipError_t launch_group_gemm(const GemmArgs& a, int phase, int grid, bool narrow, hipStream_t s);
 int group_gemm_grid(int device);
 
 // slots in the activation dtype (slot16) or fp32
