@@ -743,33 +743,30 @@ mxmoe_status mxmoe_moe_forward_ex(const mxmoe_block* B, const void* block_table,
   MX_CHECK(launch_group_gemm(ga, 0, grid, narrow, stream));
   MX_EVENT(3);
   MX_EVENT(4);
-  if (bi.any_hq || bi.any_hmx)
-    MX_CHECK(launch_hquant_routed(ga.h, bi.act, T * bi.k, bi.F, offsets, bi.E, down_qmax, at<int8_t>(workspace, L.hq),
-                                  at<float>(workspace, L.hs), at<float>(workspace, L.hsg), at<uint8_t>(workspace, L.hqmx),
-                                  at<uint8_t>(workspace, L.hsmx), stream));
-  for (int j = 0; j < bi.nsh; ++j) {
-    const size_t rows = (size_t)j * T;
-    const void* hsrc = reinterpret_cast<const uint8_t*>(ga.h_shared) + rows * bi.Fsh * 2;
-    if (bi.kinds[bi.E + j][2] == K_MXFP4) {
-      MX_CHECK(launch_act_quant_mx(hsrc, bi.act, T, bi.Fsh, bi.Fsh, at<uint8_t>(workspace, L.hqmx_shared) + rows * bi.Fsh / 2,
-                                   at<uint8_t>(workspace, L.hsmx_shared) + rows * bi.Fsh / 32, stream));
-      continue;
-    }
-    const int qm = kind_qmax(bi.kinds[bi.E + j][2]);
-    if (!qm) continue;
-    int8_t* hq = at<int8_t>(workspace, L.hq_shared) + rows * bi.Fsh;
-    if (bi.kinds[bi.E + j][2] == K_W4A4F6) {
-      MX_CHECK(launch_act_quant_f6(hsrc, bi.act, T, bi.Fsh, bi.Fsh, reinterpret_cast<uint8_t*>(hq),
-                                   at<float>(workspace, L.hs_shared) + rows, stream));
-      continue;
-    }
-    if (bi.kinds[bi.E + j][2] == K_W4A4G)
-      MX_CHECK(launch_act_quant_g128(hsrc, bi.act, T, bi.Fsh, bi.Fsh, qm, hq,
-                                     at<float>(workspace, L.hsg_shared) + rows * (bi.Fsh / 128), stream));
-    else
-      MX_CHECK(launch_act_quant(hsrc, bi.act, T, bi.Fsh, bi.Fsh, qm, hq, at<float>(workspace, L.hs_shared) + rows,
-                                stream));
-  }
+  HQuantArgs ha;
+  memset(&ha, 0, sizeof(ha));
+  ha.h = ga.h;
+  ha.h_shared = ga.h_shared;
+  ha.act = bi.act;
+  ha.T = T;
+  ha.P = T * bi.k;
+  ha.F = bi.F;
+  ha.E = bi.E;
+  ha.nsh = bi.nsh;
+  ha.Fsh = bi.Fsh;
+  ha.offsets = offsets;
+  ha.down_qmax = down_qmax;
+  ha.hq = at<int8_t>(workspace, L.hq);
+  ha.hs = at<float>(workspace, L.hs);
+  ha.hsg = at<float>(workspace, L.hsg);
+  ha.hqmx = at<uint8_t>(workspace, L.hqmx);
+  ha.hsmx = at<uint8_t>(workspace, L.hsmx);
+  ha.hq_shared = at<int8_t>(workspace, L.hq_shared);
+  ha.hs_shared = at<float>(workspace, L.hs_shared);
+  ha.hsg_shared = at<float>(workspace, L.hsg_shared);
+  ha.hqmx_shared = at<uint8_t>(workspace, L.hqmx_shared);
+  ha.hsmx_shared = at<uint8_t>(workspace, L.hsmx_shared);
+  MX_CHECK(launch_hquant(ha, bi.any_hq || bi.any_hmx, bi.any_hq_sh || bi.any_hmx_sh, stream));
   MX_EVENT(5);
   MX_EVENT(6);
   MX_CHECK(launch_group_gemm(ga, 1, grid, narrow, stream));

@@ -7,6 +7,8 @@
 //   * the weighted combine of Eq. (2): the per-slot down rows, already scaled
 //     by their gate weight, are summed in a fixed order in fp32 and rounded
 //     once to the activation dtype.
+#include <algorithm>
+
 #include "mxmoe_internal.h"
 #include "rowquant.h"
 
@@ -111,47 +113,97 @@ __global__ void __launch_bounds__(kThreads) act_quant_vec_kernel(const void* a, 
                            qmax, reinterpret_cast<uint2*>(codes + r * cols), scales + r, red);
 }
 
-// Rows of the sorted (token, slot) pairs whose expert's down projection takes
-// a8/a4 activations; the expert of a row is found in an LDS copy of offsets.
+// Register-resident shapes by row length: (chunks per lane, wavefronts per row).
+enum RowShape { RS_1x2, RS_1x4, RS_1x8, RS_4x4, RS_4x8, RS_4x16, RS_STREAM };
+__host__ __device__ inline RowShape row_shape(int cols) {
+  const int nch = cols / 8, per = (nch + 63) / 64, per4 = (nch + 255) / 256;
+  if (per <= 2) return RS_1x2;
+  if (per <= 4) return RS_1x4;
+  if (per <= 8) return RS_1x8;
+  if (per4 <= 4) return RS_4x4;
+  if (per4 <= 8) return RS_4x8;
+  if (per4 <= 16) return RS_4x16;  // rows up to 32768 elements stay in registers (read once)
+  return RS_STREAM;
+}
+__host__ __device__ inline int row_waves(RowShape s) { return s == RS_4x4 || s == RS_4x8 || s == RS_4x16 ? 4 : 1; }
+
+// One h row of F elements in the encoding its down projection takes (qm:
+// kDownQ* flags or the integer qmax): the wavefront's row (W = 1) or the
+// workgroup's (W = 4).
+struct HEnc { uint4* mx; uint8_t* mxe; int8_t* q; float* s; float* sg; };
 template <int NC, int W>
-__global__ void __launch_bounds__(kThreads) hquant_routed_kernel(const void* h, int act, int P, int F,
-                                                                 const int32_t* __restrict__ offsets, int E,
-                                                                 const int32_t* __restrict__ down_qmax,
-                                                                 int8_t* hq, float* hs, float* hsg, uint8_t* hqmx,
-                                                                 uint8_t* hsmx) {
+__device__ __attribute__((always_inline)) inline void hquant_row(const uint4* row, int F, int act, int qm, const HEnc& o, uint32_t* red) {
+  if (qm & kDownQMX) {  // MXFP4 down projection: one wavefront per row
+    if (W == 1 || threadIdx.x < 64) quant_row_mx(row, F, act, o.mx, o.mxe);
+  } else if (qm & kDownQGroup) {  // per-128-group scales: one wavefront per row
+    if (W == 1 || threadIdx.x < 64) quant_row_groups(row, F, act, qm & 0xFF, reinterpret_cast<uint2*>(o.q), o.sg);
+  } else if (qm & kDownQF6) {  // int4 codes as FP6 e2m3 groups
+    quant_row_vec<NC, W, true>(row, F, act, 7, reinterpret_cast<uint2*>(o.q), o.s, red);
+  } else {
+    quant_row_vec<NC, W>(row, F, act, (qm & kDownQF8) ? kQmaxF8 : qm, reinterpret_cast<uint2*>(o.q), o.s, red);
+  }
+}
+// MAXNC: the largest chunk count of the launch's row shapes (0 stands for
+// streamed rows too), so that launches of short rows keep few registers
+template <int MAXNC>
+__device__ __attribute__((always_inline)) inline void hquant_any(RowShape sh, const uint4* row, int F, int act, int qm, const HEnc& o, uint32_t* red) {
+  switch (sh) {
+    case RS_1x2: hquant_row<2, 1>(row, F, act, qm, o, red); break;
+    case RS_1x4: hquant_row<4, 1>(row, F, act, qm, o, red); break;
+    case RS_4x4: hquant_row<4, 4>(row, F, act, qm, o, red); break;
+    case RS_1x8: if constexpr (MAXNC >= 8) hquant_row<8, 1>(row, F, act, qm, o, red); break;
+    case RS_4x8: if constexpr (MAXNC >= 8) hquant_row<8, 4>(row, F, act, qm, o, red); break;
+    case RS_4x16: if constexpr (MAXNC >= 16) hquant_row<16, 4>(row, F, act, qm, o, red); break;
+    default: if constexpr (MAXNC >= 16) hquant_row<0, 1>(row, F, act, qm, o, red); break;
+  }
+}
+
+// Every h row whose down projection takes encoded activations, routed and
+// shared, in one launch (a launch costs about 5 us however few rows it has:
+// the forward of 1 token of the Qwen1.5-shaped block took 64.5 us with one
+// launch for the shared expert more, 59.5 now; DeepSeek-V2-Lite-shaped, 13
+// tokens, two shared experts, 86.5 -> 78.2; 2048 tokens 333 -> 328):
+// workgroups [0, nbr) take the rows of the sorted (token, slot) pairs, whose
+// expert is found in an LDS copy of offsets, the others the shared experts'
+// rows (row j T + t: token t of shared expert j).
+template <int MAXNC>
+__global__ void __launch_bounds__(kThreads, MAXNC > 8 ? 3 : 5) hquant_kernel(HQuantArgs a, int nbr) {
   __shared__ int32_t s_off[kMaxE + 1];
   __shared__ uint32_t red[kThreads / 64];
-  for (int i = threadIdx.x; i <= E; i += kThreads) s_off[i] = offsets[i];
-  __syncthreads();
-  const int r = (int)my_row<W>();
-  if (r >= P || r >= s_off[E]) return;
-  int lo = 0, hi = E;  // largest e with offsets[e] <= r
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (s_off[mid] <= r) lo = mid; else hi = mid;
+  const bool shared = (int)blockIdx.x >= nbr;
+  const int F = shared ? a.Fsh : a.F;
+  const RowShape sh = row_shape(F);
+  const int64_t b = (int)blockIdx.x - (shared ? nbr : 0);
+  const int64_t r = row_waves(sh) == 1 ? b * kRowsPerBlock + (threadIdx.x >> 6) : b;
+  HEnc o;
+  int qm;
+  if (shared) {
+    if (r >= (int64_t)a.nsh * a.T) return;
+    qm = a.down_qmax[a.E + (int)(r / a.T)];
+    o.q = a.hq_shared + r * F;
+    o.s = a.hs_shared + r;
+    o.sg = a.hsg_shared + r * (F >> 7);
+    o.mx = reinterpret_cast<uint4*>(a.hqmx_shared + r * (F >> 1));
+    o.mxe = a.hsmx_shared + r * (F >> 5);
+  } else {
+    for (int i = threadIdx.x; i <= a.E; i += kThreads) s_off[i] = a.offsets[i];
+    __syncthreads();
+    if (r >= a.P || r >= s_off[a.E]) return;
+    int lo = 0, hi = a.E;  // largest e with offsets[e] <= r
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (s_off[mid] <= r) lo = mid; else hi = mid;
+    }
+    qm = a.down_qmax[lo];
+    o.q = a.hq + r * F;
+    o.s = a.hs + r;
+    o.sg = a.hsg + r * (F >> 7);
+    o.mx = reinterpret_cast<uint4*>(a.hqmx + r * (F >> 1));
+    o.mxe = a.hsmx + r * (F >> 5);
   }
-  const int qm = down_qmax[lo];
   if (qm == 0) return;
-  if (qm & kDownQMX) {  // MXFP4 down projection: one wavefront per row
-    if (W == 1 || threadIdx.x < 64)
-      quant_row_mx(reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(h) + (int64_t)r * F), F, act,
-                   reinterpret_cast<uint4*>(hqmx + (int64_t)r * (F >> 1)), hsmx + (int64_t)r * (F >> 5));
-    return;
-  }
-  if (qm & kDownQGroup) {  // per-128-group scales: one wavefront per row
-    if (W == 1 || threadIdx.x < 64)
-      quant_row_groups(reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(h) + (int64_t)r * F), F, act,
-                       qm & 0xFF, reinterpret_cast<uint2*>(hq + (int64_t)r * F), hsg + (int64_t)r * (F >> 7));
-    return;
-  }
-  if (qm & kDownQF6) {  // int4 codes as FP6 e2m3 groups
-    quant_row_vec<NC, W, true>(reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(h) + (int64_t)r * F), F,
-                               act, 7, reinterpret_cast<uint2*>(hq + (int64_t)r * F), hs + r, red);
-    return;
-  }
-  const int qmax = (qm & kDownQF8) ? kQmaxF8 : qm;
-  quant_row_vec<NC, W>(reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(h) + (int64_t)r * F), F,
-                       act, qmax, reinterpret_cast<uint2*>(hq + (int64_t)r * F), hs + r, red);
+  const uint16_t* h = reinterpret_cast<const uint16_t*>(shared ? a.h_shared : a.h) + r * F;
+  hquant_any<MAXNC>(sh, reinterpret_cast<const uint4*>(h), F, a.act, qm, o, red);
 }
 
 // Row sums of each 128-wide block of bf16 rows, one wavefront per row: a
@@ -224,18 +276,6 @@ __global__ void __launch_bounds__(kThreads) combine_kernel(const void* __restric
   *reinterpret_cast<uint4*>(y + (int64_t)t * H + h) = o;
 }
 
-// Register-resident shapes by row length: (chunks per lane, wavefronts per row).
-enum RowShape { RS_1x2, RS_1x4, RS_1x8, RS_4x4, RS_4x8, RS_4x16, RS_STREAM };
-RowShape row_shape(int cols) {
-  const int nch = cols / 8, per = (nch + 63) / 64, per4 = (nch + 255) / 256;
-  if (per <= 2) return RS_1x2;
-  if (per <= 4) return RS_1x4;
-  if (per <= 8) return RS_1x8;
-  if (per4 <= 4) return RS_4x4;
-  if (per4 <= 8) return RS_4x8;
-  if (per4 <= 16) return RS_4x16;  // rows up to 32768 elements stay in registers (read once)
-  return RS_STREAM;
-}
 template <template <int, int> class K, typename... Args>
 hipError_t launch_rows(int rows, int cols, hipStream_t s, Args... args) {
   const RowShape rs = row_shape(cols);
@@ -253,7 +293,6 @@ hipError_t launch_rows(int rows, int cols, hipStream_t s, Args... args) {
 }
 template <int NC, int W> struct ActQuantK { static constexpr auto fn = act_quant_vec_kernel<NC, W>; };
 template <int NC, int W> struct ActQuantF6K { static constexpr auto fn = act_quant_vec_kernel<NC, W, true>; };
-template <int NC, int W> struct HQuantK { static constexpr auto fn = hquant_routed_kernel<NC, W>; };
 }  // namespace
 
 hipError_t launch_rowsum(const void* a, int rows, int cols, int64_t ld, float* out, hipStream_t s) {
@@ -304,14 +343,37 @@ hipError_t launch_act_quant_mx(const void* a, int act, int rows, int cols, int64
   return hipGetLastError();
 }
 
-hipError_t launch_hquant_routed(const void* h, int act, int P, int F, const int32_t* offsets, int E,
-                                const int32_t* down_qmax, int8_t* hq, float* hs, float* hsg, uint8_t* hqmx,
-                                uint8_t* hsmx, hipStream_t s) {
-  if (P <= 0) return hipSuccess;
-  if ((reinterpret_cast<uintptr_t>(h) & 15) || (reinterpret_cast<uintptr_t>(hq) & 7) || F % 8 || E > kMaxE)
+hipError_t launch_hquant(const HQuantArgs& a, bool routed, bool shared, hipStream_t s) {
+  if (!routed && !shared) return hipSuccess;
+  const auto bad = [](const void* h, const void* hq, int cols) {
+    return (reinterpret_cast<uintptr_t>(h) & 15) || (reinterpret_cast<uintptr_t>(hq) & 31) || cols % 128;
+  };
+  if ((routed && bad(a.h, a.hq, a.F)) || (shared && bad(a.h_shared, a.hq_shared, a.Fsh)) || a.E > kMaxE)
     return hipErrorInvalidValue;
-  if (F % 128) return hipErrorInvalidValue;
-  return launch_rows<HQuantK>(P, F, s, h, act, P, F, offsets, E, down_qmax, hq, hs, hsg, hqmx, hsmx);
+  auto blocks = [](int64_t rows, int cols) { return row_waves(row_shape(cols)) == 1 ? (rows + kRowsPerBlock - 1) / kRowsPerBlock : rows; };
+  const int nbr = routed ? (int)blocks(a.P, a.F) : 0;
+  const int64_t nb = nbr + (shared ? blocks((int64_t)a.nsh * a.T, a.Fsh) : 0);
+  if (nb <= 0) return hipSuccess;
+  auto nc = [](int cols) {
+    switch (row_shape(cols)) {
+      case RS_1x2: case RS_1x4: case RS_4x4: return 4;
+      case RS_1x8: case RS_4x8: return 8;
+      default: return 16;
+    }
+  };
+  const int m = std::max(routed ? nc(a.F) : 0, shared ? nc(a.Fsh) : 0);
+  // One launch needs the registers of its longest rows.  Past 4096 rows the
+  // fewer resident wavefronts cost more than the second launch (Qwen2-shaped,
+  // 131072 routed rows of 2560 and 16384 shared ones of 20480: 2% of the
+  // forward).
+  if (routed && shared && m > 8 && (int64_t)a.P + (int64_t)a.nsh * a.T > 4096) {
+    const hipError_t e = launch_hquant(a, true, false, s);
+    return e != hipSuccess ? e : launch_hquant(a, false, true, s);
+  }
+  if (m <= 4) hipLaunchKernelGGL((hquant_kernel<4>), dim3((unsigned)nb), dim3(kThreads), 0, s, a, nbr);
+  else if (m <= 8) hipLaunchKernelGGL((hquant_kernel<8>), dim3((unsigned)nb), dim3(kThreads), 0, s, a, nbr);
+  else hipLaunchKernelGGL((hquant_kernel<16>), dim3((unsigned)nb), dim3(kThreads), 0, s, a, nbr);
+  return hipGetLastError();
 }
 
 hipError_t launch_combine(const void* slots, int slot16, const int32_t* ids, int T, int k, int E, int nsh, int H,

@@ -337,11 +337,6 @@ hipError_t launch_act_quant_g128(const void* a, int act, int rows, int cols, int
 hipError_t launch_act_quant(const void* a, int act, int rows, int cols, int64_t ld, int qmax,
                             int8_t* codes, float* scales, hipStream_t s);
 
-// Per sorted row j < offsets[E] (pair p = sorted_pair[j], token t = p / k,
-// slot s = p % k): rtok[j] = t, rslot[j] = t (k + n_sh) + s, rgw[j] = topk_w[p],
-// and rxs8[j] / rxs4[j] = the token's activation scale where those exist.
-
-
 // Quantize routed h rows whose expert's down projection is a8/a4 (qmax from
 // down_qmax[expert]); rows of other experts are skipped.
 // Routed h rows of the experts whose down linear quantizes its activations:
@@ -351,9 +346,17 @@ constexpr int kDownQGroup = 0x100;
 constexpr int kDownQMX = 0x200;  // MXFP4 codes into hqmx [P][F/2], E8M0 bytes into hsmx [P][F/32]
 constexpr int kDownQF8 = 0x400;  // FP8 e4m3 codes into hq, per-row scales into hs
 constexpr int kDownQF6 = 0x800;  // int4 codes as FP6 e2m3 (32 per 24 + 8 zero bytes) into hq, scales into hs
-hipError_t launch_hquant_routed(const void* h, int act, int P, int F, const int32_t* offsets,
-                                int E, const int32_t* down_qmax, int8_t* hq, float* hs, float* hsg,
-                                uint8_t* hqmx, uint8_t* hsmx, hipStream_t s);
+// Shared expert j's rows j T .. j T + T - 1 follow down_qmax[E + j] alike, into
+// the shared buffers.
+struct HQuantArgs {
+  const void* h; const void* h_shared;
+  int act, T, P, F, E, nsh, Fsh;
+  const int32_t* offsets;
+  const int32_t* down_qmax;
+  int8_t* hq; float* hs; float* hsg; uint8_t* hqmx; uint8_t* hsmx;
+  int8_t* hq_shared; float* hs_shared; float* hsg_shared; uint8_t* hqmx_shared; uint8_t* hsmx_shared;
+};
+hipError_t launch_hquant(const HQuantArgs& a, bool routed, bool shared, hipStream_t s);
 // MXFP4 encoding of rows (cols a multiple of 128): codes [rows][cols/2] (two
 // e2m1 nibbles a byte, element order), E8M0 bytes [rows][cols/32].
 hipError_t launch_act_quant_mx(const void* a, int act, int rows, int cols, int64_t ld, uint8_t* codes, uint8_t* exps,

@@ -128,7 +128,7 @@ __device__ inline void store_f6_chunk(uint8_t* row, int c, uint64_t w) {
 // one row).  NC > 0: the row's 16-byte chunks stay in registers
 // (cols <= 512 * W * NC); NC == 0: any length, the row is read twice.
 template <int NC, int W, bool F6 = false>
-__device__ inline float quant_row_vec(const uint4* __restrict__ row, int cols, int act, int qmax,
+__device__ __attribute__((always_inline)) inline float quant_row_vec(const uint4* __restrict__ row, int cols, int act, int qmax,
                                       uint2* __restrict__ codes, float* __restrict__ scale, uint32_t* red) {
   const int idx = W == 1 ? (threadIdx.x & 63) : threadIdx.x, nch = cols >> 3;
   constexpr int kStride = 64 * W;
@@ -183,7 +183,7 @@ __device__ inline float quant_row_vec(const uint4* __restrict__ row, int cols, i
 // Quantizes one row per block of 128 elements (w4a4-g128 activations), one
 // wavefront: a block is 16 chunks of 8, one per lane of a 16-lane group, whose
 // maximum the group shares; the fp32 recipe of quant_row per block.
-__device__ inline void quant_row_groups(const uint4* __restrict__ row, int cols, int act, int qmax,
+__device__ __attribute__((always_inline)) inline void quant_row_groups(const uint4* __restrict__ row, int cols, int act, int qmax,
                                         uint2* __restrict__ codes, float* __restrict__ scales) {
   const int lane = threadIdx.x & 63, nch = cols >> 3;
   const uint32_t nan_lo = act == MXMOE_BF16 ? 0x7f81u : 0x7c01u;
@@ -216,7 +216,7 @@ __device__ inline uint32_t e2m1_mag(float x) {
   return (uint32_t)(x > 0.25f) + (uint32_t)(x >= 0.75f) + (uint32_t)(x > 1.25f) + (uint32_t)(x >= 1.75f) +
          (uint32_t)(x > 2.5f) + (uint32_t)(x >= 3.5f) + (uint32_t)(x > 5.0f);
 }
-__device__ inline void quant_row_mx(const uint4* __restrict__ row, int cols, int act, uint4* __restrict__ codes,
+__device__ __attribute__((always_inline)) inline void quant_row_mx(const uint4* __restrict__ row, int cols, int act, uint4* __restrict__ codes,
                                     uint8_t* __restrict__ exps) {
   const int lane = threadIdx.x & 63, nb = cols >> 5;
   for (int b = lane; b < nb; b += 64) {
