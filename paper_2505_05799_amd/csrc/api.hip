@@ -456,7 +456,7 @@ mxmoe_status mxmoe_linear_forward(const mxmoe_linear* L, mxmoe_dtype act, const 
   XPrep nox;
   memset(&nox, 0, sizeof(nox));
   const bool narrow = narrow_launch(tiles_bound(1, m, L->n, 256), codes_bytes(kd, L->n, L->k));
-  hipError_t e = launch_plan(nullptr, 1, 1, m, nullptr, nullptr, m, dl, nullptr, ga.plan, w.qcap, w.fcap, w.pfloats,
+  hipError_t e = launch_plan(nullptr, 1, 1, m, nullptr, nullptr, nullptr, m, dl, nullptr, ga.plan, w.qcap, w.fcap, w.pfloats,
                              nullptr, grid, narrow, nox, stream);
   if (e != hipSuccess) return MXMOE_ERR_HIP;
   return hip_status(launch_group_gemm(ga, 2, grid, narrow, stream));
@@ -624,23 +624,32 @@ mxmoe_status mxmoe_moe_forward_ex(const mxmoe_block* B, const void* block_table,
   rm.rtok = at<int32_t>(workspace, L.rtok);
   rm.rslot = at<int32_t>(workspace, L.rslot);
   rm.rgw = at<float>(workspace, L.rgw);
-  if (router) {  // in the routing launch where the batch allows
+  if (router) {
     int32_t* rids = at<int32_t>(workspace, L.rids);
     float* rw = at<float>(workspace, L.rw);
     float* rshw = (bi.nsh && opts->shared_logits) ? at<float>(workspace, L.shw) : nullptr;
-    MX_CHECK(launch_router_route(opts->router_logits, T, bi.E, bi.k, opts->renormalize,
-                                 rshw ? opts->shared_logits : nullptr, bi.nsh, rids, rw, rshw, counts, offsets,
-                                 sorted_pair, at<int32_t>(workspace, L.inv), at<int32_t>(workspace, L.status),
-                                 at<int32_t>(workspace, L.chunk_counts), at<int32_t>(workspace, L.chunk_bad), &rm,
-                                 stream));
     ids = rids;
     tw = rw;
     shw = rshw;
-  } else {
+  }
+  rm.topk_w = tw;
+  RouteJob job = route_job(ids, T, bi.k, bi.E, counts, offsets, sorted_pair, at<int32_t>(workspace, L.inv),
+                           at<int32_t>(workspace, L.status), &rm);
+  // Small batches: the plan launch does the routing first, and the router where
+  // a token's logits fit a group of lanes.
+  const bool fused = (int64_t)T * bi.k <= kRouteSmall && bi.G <= kSmallG;
+  if (router) {
+    const RouterArgs ra{opts->router_logits, bi.k, opts->renormalize, shw ? opts->shared_logits : nullptr, bi.nsh,
+                        at<int32_t>(workspace, L.rids), at<float>(workspace, L.rw), at<float>(workspace, L.shw)};
+    if (fused && router_by_group(bi.E, bi.k)) job.ra = ra;
+    else
+      MX_CHECK(launch_router_topk(ra.logits, T, bi.E, bi.k, ra.renorm, ra.shared_logits, bi.nsh, ra.ids, ra.w,
+                                  ra.shared_w, stream));
+  }
+  if (!fused)
     MX_CHECK(launch_route(ids, T, bi.k, bi.E, counts, offsets, sorted_pair, at<int32_t>(workspace, L.inv),
                           at<int32_t>(workspace, L.status), at<int32_t>(workspace, L.chunk_counts),
                           at<int32_t>(workspace, L.chunk_bad), &rm, stream));
-  }
   const bool narrow = narrow_block(bi, T);
   DevLinear none;
   memset(&none, 0, sizeof(none));
@@ -679,11 +688,12 @@ mxmoe_status mxmoe_moe_forward_ex(const mxmoe_block* B, const void* block_table,
     xp.sf6 = at<float>(workspace, L.xsf6);
   }
   // the x encodings also copy the per-token scales to the token's sorted rows
+  // (not where the same launch does the routing, which they do not wait for)
   xp.inv = at<int32_t>(workspace, L.inv);
   xp.k = bi.k;
-  if (xp.q8) xp.r8 = at<float>(workspace, L.rxs8);
-  if (xp.q4) xp.r4 = at<float>(workspace, L.rxs4);
-  MX_CHECK(launch_plan(experts, bi.E, bi.G, T, counts, offsets, -1, none, mask, plan, L.qcap, L.fcap, L.pfloats,
+  if (xp.q8 && !fused) xp.r8 = at<float>(workspace, L.rxs8);
+  if (xp.q4 && !fused) xp.r4 = at<float>(workspace, L.rxs4);
+  MX_CHECK(launch_plan(experts, bi.E, bi.G, T, fused ? &job : nullptr, counts, offsets, -1, none, mask, plan, L.qcap, L.fcap, L.pfloats,
                        down_qmax, grid, narrow, xp, stream));
   GemmArgs ga;
   memset(&ga, 0, sizeof(ga));
@@ -718,8 +728,8 @@ mxmoe_status mxmoe_moe_forward_ex(const mxmoe_block* B, const void* block_table,
   ga.rtok = at<int32_t>(workspace, L.rtok);
   ga.rslot = at<int32_t>(workspace, L.rslot);
   ga.rgw = at<float>(workspace, L.rgw);
-  ga.rxs8 = at<float>(workspace, L.rxs8);
-  ga.rxs4 = at<float>(workspace, L.rxs4);
+  ga.rxs8 = xp.r8;
+  ga.rxs4 = xp.r4;
   ga.partial = at<float>(workspace, L.partial);
   ga.rsx = at<float>(workspace, L.rsx);
   ga.xq4g = at<int8_t>(workspace, L.xq4g);

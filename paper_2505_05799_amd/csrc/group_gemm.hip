@@ -2,7 +2,8 @@
 // micro-kernels themselves are in group_gemm_impl.h, one translation unit per
 // activation dtype and phase).
 //
-// plan_kernel (one workgroup, no host round trip):
+// plan_kernel (a workgroup per phase, no host round trip; the routing of a small
+// batch comes first in the same launch):
 //   1. per (phase, expert) group: rows m (routing counts, T for shared experts),
 //      tile configuration from m, tile counts, the per-tile cost from the
 //      cost table (tile_cost);
@@ -17,9 +18,12 @@
 // Groups may be sliced along the reduction (split-K, kSplitShare / kSplitMinKb): their
 // slices are queued as extra channel tiles, within fixed budgets of added
 // tiles and of partial-sum storage.
+#include <string.h>
+
 #include <mutex>
 
 #include "group_gemm_impl.h"
+#include "route_impl.h"
 #include "rowquant.h"
 
 namespace mxmoe {
@@ -48,86 +52,103 @@ __device__ inline SuperDims plan_super_dims(int mt, int nt) {
   return d;
 }
 
-__global__ void __launch_bounds__(1024) plan_kernel(const DevExpert* __restrict__ experts, int E, int G, int T,
+// MG: groups the workgroup's arrays hold; ROUTE: the routing of a small batch
+// (job) comes first, done whole by workgroup 0 and up to the counts by 1.
+template <int MG, bool ROUTE>
+__global__ void __launch_bounds__(1024) plan_kernel(RouteJob job, const DevExpert* __restrict__ experts, int E, int G, int T,
                                                     const int32_t* __restrict__ counts,
                                                     const int32_t* __restrict__ offsets, int raw_m,
                                                     DevLinear raw_lin, MaskBits mask, int32_t* __restrict__ plan,
                                                     int qcap, int fcap, int64_t pfloats,
                                                     int32_t* __restrict__ down_qmax, int nwg, int nsub, XPrep xp,
                                                     TileCosts tc) {
-  // workgroups 1.. encode x, one row per wavefront (grid-stride); the plan
-  // below runs on workgroup 0 alone
-  if (blockIdx.x > 0) {
-    const int64_t nw = (int64_t)(gridDim.x - 1) * (blockDim.x >> 6);
-    for (int64_t r = (int64_t)(blockIdx.x - 1) * (blockDim.x >> 6) + (threadIdx.x >> 6); r < xp.rows; r += nw)
+  // workgroup p < nphase plans phase p; the others encode x, one row per
+  // wavefront (grid-stride)
+  const int nphase = raw_m >= 0 ? 1 : 2;
+  if ((int)blockIdx.x >= nphase) {
+    const int64_t nw = (int64_t)(gridDim.x - nphase) * (blockDim.x >> 6);
+    for (int64_t r = (int64_t)(blockIdx.x - nphase) * (blockDim.x >> 6) + (threadIdx.x >> 6); r < xp.rows; r += nw)
       x_prep_row(xp, r);
     return;
   }
+  const int ph = blockIdx.x;
   // Every per-group input is read from global memory once, into LDS; the steps
   // below work from LDS and only write the plan out, so their barriers wait
   // for LDS traffic only and the plan's stores drain in the background.
-  __shared__ int32_t s_m[kMaxG];          // rows of each group (0 if masked)
-  __shared__ int32_t s_off[kMaxG];        // first sorted row (routed groups)
-  __shared__ int32_t s_n[2][kMaxG];       // output channels of the phase's linear
-  __shared__ int32_t s_kb[2][kMaxG];      // its 128-wide k blocks
-  __shared__ int8_t s_kd[2][kMaxG];       // its micro-kernel kind
-  __shared__ int8_t s_sp[2][kMaxG];       // slices: proposed (| 16 if by the fallback), then final
-  __shared__ int32_t s_cost[2][kMaxG];    // budget need, then tile cost
-  __shared__ int32_t s_tiles[2][kMaxG];   // sliced output tiles, then queued tiles
-  __shared__ int32_t s_order[2][kMaxG];   // group per rank
-  __shared__ int32_t s_c1[2][kMaxG];      // unsliced tile cost
-  __shared__ int32_t s_cs[2][kMaxG];      // tile cost with the proposed slices
-  __shared__ int64_t s_work[2][1024 / 64];
-  __shared__ int64_t s_theta[2];          // slicing threshold per phase
-  __shared__ int32_t s_ut[2][1024 / 64];  // unsliced tiles per wavefront, then per phase in [p][0]
-  __shared__ int32_t s_used[2];           // output-tile counters used per phase
+  __shared__ int32_t s_m[MG];          // rows of each group (0 if masked)
+  __shared__ int32_t s_off[MG];        // first sorted row (routed groups)
+  __shared__ int32_t s_n[MG];       // output channels of the phase's linear
+  __shared__ int32_t s_kb[MG];      // its 128-wide k blocks
+  __shared__ int8_t s_kd[MG];       // its micro-kernel kind
+  __shared__ int8_t s_sp[MG];       // slices: proposed (| 16 if by the fallback), then final
+  __shared__ int32_t s_cost[MG];    // budget need, then tile cost
+  __shared__ int32_t s_tiles[MG];   // sliced output tiles, then queued tiles
+  __shared__ int32_t s_order[MG];   // group per rank
+  __shared__ int32_t s_c1[MG];      // unsliced tile cost
+  __shared__ int32_t s_cs[MG];      // tile cost with the proposed slices
+  __shared__ int64_t s_work[1024 / 64];
+  __shared__ int64_t s_theta;             // slicing threshold
+  __shared__ int32_t s_ut[1024 / 64];     // unsliced tiles per wavefront, then of the phase in [0]
+  __shared__ int32_t s_used;              // output-tile counters used
   __shared__ int32_t s_tc[kCostEntries];  // tile cost table
-  __shared__ int32_t s_ng[2];             // groups with tiles per phase
-  __shared__ int32_t s_nst[2];            // super-tiles per phase
+  __shared__ int32_t s_ng;                // groups with tiles
+  __shared__ int32_t s_nst;               // super-tiles
+  __shared__ std::conditional_t<ROUTE, RouteLds<MG>, int> s_route;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nwave = blockDim.x >> 6;
-  const int nphase = raw_m >= 0 ? 1 : 2;
   const PlanLayout PL = plan_layout(G, qcap, fcap);
   int32_t* misc = plan + PL.misc;
   int32_t* order = plan + PL.order;
   auto rec_of = [&](int ph, int g) { return plan + PL.rec + ((int64_t)ph * G + g) * PF_N; };
 
-  // 0. inputs (and the cost table)
-  for (int i = tid; i < kCostEntries; i += blockDim.x) s_tc[i] = tc.v[i];
-  for (int g = tid; g < G; g += blockDim.x) {
-    int m = raw_m >= 0 ? raw_m : (g < E ? counts[g] : T);
-    if (!((mask.w[g >> 5] >> (g & 31)) & 1u)) m = 0;
-    s_m[g] = m;
-    s_off[g] = (raw_m < 0 && g < E) ? offsets[g] : 0;
-    for (int ph = 0; ph < nphase; ++ph) {
-      const DevLinear& L = raw_m >= 0 ? raw_lin : experts[g].lin[ph == 0 ? 0 : 2];
-      s_n[ph][g] = L.n;
-      s_kb[ph][g] = L.k / 128;
-      s_kd[ph][g] = (int8_t)L.kind;
+  // 0. inputs (and the cost table).  With ROUTE the upper half of the workgroup
+  //    reads them (G <= 512) while the lower half waits for its pairs' ids.
+  const int t0 = ROUTE ? tid - 512 : tid;
+  for (int i = t0; i >= 0 && i < kCostEntries; i += ROUTE ? 512 : (int)blockDim.x) s_tc[i] = tc.v[i];
+  for (int g = t0; g >= 0 && g < G; g += ROUTE ? 512 : (int)blockDim.x) {
+    const bool live = (mask.w[g >> 5] >> (g & 31)) & 1u;
+    if (!ROUTE || g >= E) {
+      const int m = raw_m >= 0 ? raw_m : (g < E ? counts[g] : T);
+      s_m[g] = live ? m : 0;
+      s_off[g] = (raw_m < 0 && g < E) ? offsets[g] : 0;
     }
-    if (raw_m < 0) {
-      const int dk = experts[g].lin[2].kind;
+    const DevLinear& L = raw_m >= 0 ? raw_lin : experts[g].lin[ph == 0 ? 0 : 2];
+    s_n[g] = L.n;
+    s_kb[g] = L.k / 128;
+    s_kd[g] = (int8_t)L.kind;
+    if (raw_m < 0 && ph == 1) {
+      const int dk = L.kind;
       down_qmax[g] = dk == K_MXFP4 ? kDownQMX
                     : (dk == K_F8A8 ? kDownQF8
                                     : (kind_qmax(dk) | (dk == K_W4A4G ? kDownQGroup : 0) | (dk == K_W4A4F6 ? kDownQF6 : 0)));
     }
   }
-  if (tid < 2) s_ng[tid] = 0;
+  if constexpr (ROUTE) {
+    int c, f;
+    route_block<MG>(s_route, job, ph == 0, &c, &f);
+    if (tid < E) {
+      s_m[tid] = ((mask.w[tid >> 5] >> (tid & 31)) & 1u) ? c : 0;
+      s_off[tid] = f;
+    }
+  }
   if (tid == 0) {
-    misc[4] = 0;
-    misc[8] = nwg;
+    s_ng = 0;
+    if (ph == 0) {
+      misc[4] = 0;
+      misc[8] = nwg;
+    }
   }
   lds_barrier();
   struct Geom { int m, cfg, bm, bn, mt, nt, kb, kd, nl, ce; };
   auto geom = [&](int ph, int g) {
     Geom q;
     q.m = s_m[g];
-    q.cfg = pick_cfg(q.m, s_kd[ph][g], raw_m >= 0 ? 0 : ph);
+    q.cfg = pick_cfg(q.m, s_kd[g], raw_m >= 0 ? 0 : ph);
     q.bm = cfg_bm(q.cfg);
     q.bn = cfg_bn(q.cfg, raw_m >= 0 ? 1 : ph);  // raw mode: one linear
     q.mt = q.m > 0 ? div_small(q.m + q.bm - 1, q.bm) : 0;
-    q.nt = div_small(s_n[ph][g] + q.bn - 1, q.bn);
-    q.kb = s_kb[ph][g];
-    q.kd = s_kd[ph][g];
+    q.nt = div_small(s_n[g] + q.bn - 1, q.bn);
+    q.kb = s_kb[g];
+    q.kd = s_kd[g];
     q.nl = (raw_m < 0 && ph == 0) ? 2 : 1;
     q.ce = cost_index(raw_m >= 0 ? 1 : ph, q.kd, q.cfg);  // raw mode: one linear
     return q;
@@ -139,14 +160,14 @@ __global__ void __launch_bounds__(1024) plan_kernel(const DevExpert* __restrict_
   //    the proposed slices and, for the budget pass, the partial-sum floats
   //    (capped at pfloats + 1, which no budget admits) and the output tiles
   //    of every group that would be sliced
-  for (int ph = 0; ph < nphase; ++ph) {
+  {
     int64_t w = 0;
     int u = 0;
     for (int g = tid; g < G; g += blockDim.x) {
       const Geom q = geom(ph, g);
       const int tiles = q.mt * q.nt;
       const int32_t c = tiles > 0 ? tile_cost(s_tc + q.ce, q.kb, 1, q.mt) : 0;
-      s_c1[ph][g] = c;
+      s_c1[g] = c;
       w += (int64_t)tiles * c;
       u += tiles;
     }
@@ -155,39 +176,39 @@ __global__ void __launch_bounds__(1024) plan_kernel(const DevExpert* __restrict_
       u += __shfl_xor(u, d, 64);
     }
     if (lane == 0) {
-      s_work[ph][wave] = w;
-      s_ut[ph][wave] = u;
+      s_work[wave] = w;
+      s_ut[wave] = u;
     }
   }
   lds_barrier();
-  if (wave < nphase) {  // wavefront p sums phase p's per-wavefront totals
-    int64_t work = lane < nwave ? s_work[wave][lane] : 0;
-    int ut = lane < nwave ? s_ut[wave][lane] : 0;
+  if (wave == 0) {  // the per-wavefront totals
+    int64_t work = lane < nwave ? s_work[lane] : 0;
+    int ut = lane < nwave ? s_ut[lane] : 0;
     for (int d = 32; d > 0; d >>= 1) {
       work += __shfl_xor(work, d, 64);
       ut += __shfl_xor(ut, d, 64);
     }
     if (lane == 0) {
-      s_theta[wave] = work / nwg / kSplitShare;
-      s_ut[wave][0] = ut;
+      s_theta = (int64_t)((uint64_t)work / (uint64_t)((int64_t)nwg * kSplitShare));
+      s_ut[0] = ut;
     }
   }
   lds_barrier();
   // The slice rule (kSplitShare, kSplitMinKb), evaluated by eight lanes per group: lane
   // j prices j + 1 slices; the group takes the fewest slices whose tile cost
   // is within theta, else the cheapest (the fewest slices among equals).
-  for (int base = 0; base < nphase * G; base += (int)blockDim.x / 8) {
+  for (int base = 0; base < G; base += (int)blockDim.x / 8) {
     const int item = base + tid / 8, s = (tid & 7) + 1;
-    const bool live = item < nphase * G;
-    const int ph = live && item >= G ? 1 : 0, g = live ? item - ph * G : 0;
+    const bool live = item < G;
+    const int g = live ? item : 0;
     const Geom q = geom(ph, g);
     const bool tiled = live && q.mt * q.nt > 0;
     int smax = q.kb / kSplitMinKb;
     smax = smax < 1 ? 1 : (smax > kSplitMax ? kSplitMax : smax);
     const bool ok = tiled && s <= smax;
     int32_t c = 0;
-    if (ok) c = s == 1 ? s_c1[ph][g] : tile_cost(s_tc + q.ce, (q.kb + s - 1) / s, s, q.mt);
-    int first = (ok && c <= s_theta[ph]) ? s : 64;
+    if (ok) c = s == 1 ? s_c1[g] : tile_cost(s_tc + q.ce, (q.kb + s - 1) / s, s, q.mt);
+    int first = (ok && c <= s_theta) ? s : 64;
     int64_t key = ok ? (((int64_t)c << 8) | s) : INT64_MAX;
     for (int d = 1; d < 8; d <<= 1) {
       first = min(first, __shfl_xor(first, d, 64));
@@ -199,7 +220,7 @@ __global__ void __launch_bounds__(1024) plan_kernel(const DevExpert* __restrict_
     const int32_t c_first = __shfl(c, (lane & ~7) + (first <= kSplitMax ? first - 1 : 0), 64);
     if (live && s == 1) {
       int sp = 1;
-      int32_t csp = s_c1[ph][g];
+      int32_t csp = s_c1[g];
       if (tiled) {
         if (first <= kSplitMax) {
           sp = first;
@@ -217,10 +238,10 @@ __global__ void __launch_bounds__(1024) plan_kernel(const DevExpert* __restrict_
       r[PF_NTILES] = q.nt;
       r[PF_START] = 0;
       const int64_t need = (int64_t)q.mt * q.nt * sp * q.bm * q.bn * q.nl;
-      s_sp[ph][g] = (int8_t)(sp | (tiled && first > kSplitMax && sp > 1 ? 16 : 0));
-      s_cs[ph][g] = csp;
-      s_tiles[ph][g] = sp > 1 ? q.mt * q.nt : 0;
-      s_cost[ph][g] = sp > 1 ? (int32_t)(need <= pfloats ? need : pfloats + 1) : 0;
+      s_sp[g] = (int8_t)(sp | (tiled && first > kSplitMax && sp > 1 ? 16 : 0));
+      s_cs[g] = csp;
+      s_tiles[g] = sp > 1 ? q.mt * q.nt : 0;
+      s_cost[g] = sp > 1 ? (int32_t)(need <= pfloats ? need : pfloats + 1) : 0;
     }
   }
   lds_barrier();
@@ -235,9 +256,8 @@ __global__ void __launch_bounds__(1024) plan_kernel(const DevExpert* __restrict_
   //    unsliced.  One wavefront per phase takes 64 groups at a time; in a
   //    chunk whose partial sums and added tiles fit whole the fallback rule
   //    is one prefix sum, any other chunk is decided group by group.
-  if (wave < nphase) {
-    const int ph = wave;
-    const int64_t ut = s_ut[ph][0];
+  if (wave == 0) {
+    const int64_t ut = s_ut[0];
     int64_t pused = 0;
     int eused = 0, cused = 0;
     bool stopped = false;  // a fallback group was refused (wave-uniform)
@@ -254,11 +274,11 @@ __global__ void __launch_bounds__(1024) plan_kernel(const DevExpert* __restrict_
     };
     for (int c0 = 0; c0 < G; c0 += 64) {
       const int g = c0 + lane;
-      const int spv = g < G ? s_sp[ph][g] : 1;
+      const int spv = g < G ? s_sp[g] : 1;
       const int sp = spv & 15;
       const bool fb = (spv & 16) != 0;
-      const int tl = g < G ? s_tiles[ph][g] : 0;  // 0 unless sliced
-      const int64_t need = g < G ? s_cost[ph][g] : 0;
+      const int tl = g < G ? s_tiles[g] : 0;  // 0 unless sliced
+      const int64_t need = g < G ? s_cost[g] : 0;
       const int extra = tl * (sp - 1) <= kSplitExtra ? tl * (sp - 1) : kSplitExtra + 1;
       int64_t pin = need;
       int ein = extra, cin = tl;
@@ -313,53 +333,53 @@ __global__ void __launch_bounds__(1024) plan_kernel(const DevExpert* __restrict_
         r[PF_SPLIT] = take ? sp : 1;
         r[PF_PBASE] = take ? (int32_t)pbase : 0;
         r[PF_CBASE] = take ? cbase : 0;
-        s_sp[ph][g] = (int8_t)(take ? sp : 1);
+        s_sp[g] = (int8_t)(take ? sp : 1);
       }
     }
     if (lane == 0) {
-      s_used[ph] = cused;
+      s_used = cused;
       misc[6 + ph] = (int32_t)pused;
     }
   }
   lds_barrier();
   // 3. per-tile cost with the final slices (priced in step 1), arrival
   //    counters cleared
-  for (int ph = 0; ph < nphase; ++ph) {
+  {
     for (int g = tid; g < G; g += blockDim.x) {
       const Geom q = geom(ph, g);
-      const int sp = s_sp[ph][g];
+      const int sp = s_sp[g];
       const int tiles = q.mt * q.nt * sp;
-      const int c = tiles ? (sp > 1 ? s_cs[ph][g] : s_c1[ph][g]) : 0;
+      const int c = tiles ? (sp > 1 ? s_cs[g] : s_c1[g]) : 0;
       rec_of(ph, g)[PF_COST] = c;
-      s_cost[ph][g] = c;
-      s_tiles[ph][g] = tiles;
-      if (tiles > 0) atomicAdd(&s_ng[ph], 1);
+      s_cost[g] = c;
+      s_tiles[g] = tiles;
+      if (tiles > 0) atomicAdd(&s_ng, 1);
     }
     int32_t* cnt = plan + PL.cnt + (int64_t)ph * kSplitExtra;
-    for (int i = tid; i < s_used[ph] * nsub; i += blockDim.x) cnt[i] = 0;
+    for (int i = tid; i < s_used * nsub; i += blockDim.x) cnt[i] = 0;
   }
   lds_barrier();
   // 4. rank the groups by decreasing tile cost (ties: lower group first):
   //    one wavefront per group, each lane tests the groups of one chunk of 64
   //    and a ballot counts those ahead; the first chunk's costs stay in
   //    registers across the wavefront's groups of a phase
-  for (int ph = 0; ph < nphase; ++ph) {
-    const int own_c = lane < G ? s_cost[ph][lane] : 0;
-    const bool own_l = lane < G && s_tiles[ph][lane] > 0;
+  {
+    const int own_c = lane < G ? s_cost[lane] : 0;
+    const bool own_l = lane < G && s_tiles[lane] > 0;
     for (int g = wave; g < G; g += nwave) {
       int rank = -1;
-      if (s_tiles[ph][g] > 0) {
-        const int cg = s_cost[ph][g];
+      if (s_tiles[g] > 0) {
+        const int cg = s_cost[g];
         int ahead = 0;
         for (int c0 = 0; c0 < G; c0 += 64) {
           const int h = c0 + lane;
-          const int ch = c0 == 0 ? own_c : (h < G ? s_cost[ph][h] : 0);
-          const bool live = c0 == 0 ? own_l : (h < G && s_tiles[ph][h] > 0);
+          const int ch = c0 == 0 ? own_c : (h < G ? s_cost[h] : 0);
+          const bool live = c0 == 0 ? own_l : (h < G && s_tiles[h] > 0);
           ahead += __popcll(__ballot(live && (ch > cg || (ch == cg && h < g))));
         }
         rank = ahead;
         if (lane == 0) {
-          s_order[ph][rank] = g;
+          s_order[rank] = g;
           order[(int64_t)ph * G + rank] = g;
         }
       }
@@ -367,55 +387,56 @@ __global__ void __launch_bounds__(1024) plan_kernel(const DevExpert* __restrict_
     }
   }
   lds_barrier();
-  // 5. super-tiles dealt to the XCD queues, 6. expanded to tile entries;
-  //    both phases at once (waves 8p .. 8p + 7 build the queues of phase p).
-  //    s_cost is free from here on: s_cost[p][r] holds the super-tile count
-  //    of rank r, then its exclusive prefix sum (first global super-tile).
+  // 5. super-tiles dealt to the XCD queues, 6. expanded to tile entries.
+  //    s_cost is free from here on: s_cost[r] holds the super-tile count of
+  //    rank r, then its exclusive prefix sum (first global super-tile).
   auto dims = [&](int ph, int g, int* mt, int* ntv) {  // row tiles, channel tiles x slices
     const Geom q = geom(ph, g);
     *mt = q.mt;
-    *ntv = q.nt * s_sp[ph][g];
+    *ntv = q.nt * s_sp[g];
   };
-  for (int ph = 0; ph < nphase; ++ph) {
-    const int ng = s_ng[ph];
+  {
+    const int ng = s_ng;
     for (int r = ng + tid; r < G; r += blockDim.x) order[(int64_t)ph * G + r] = -1;
     for (int r = tid; r < ng; r += blockDim.x) {
       int mt, ntv;
-      dims(ph, s_order[ph][r], &mt, &ntv);
+      dims(ph, s_order[r], &mt, &ntv);
       const SuperDims dd = plan_super_dims(mt, ntv);
-      s_cost[ph][r] = (mt > 0 && ntv > 0) ? dd.nsm * dd.nsn : 0;
+      s_cost[r] = (mt > 0 && ntv > 0) ? dd.nsm * dd.nsn : 0;
     }
   }
   lds_barrier();
   // exclusive prefix sums of the super-tile counts in rank order, one
   //    wavefront per phase, 64 ranks at a time
-  if (wave < nphase) {
-    const int ph = wave, n = s_ng[ph];
+  if (wave == 0) {
+    const int n = s_ng;
     int run = 0;
     for (int c0 = 0; c0 < n; c0 += 64) {
       const int i = c0 + lane;
-      const int v = i < n ? s_cost[ph][i] : 0;
+      const int v = i < n ? s_cost[i] : 0;
       int incl = v;
       for (int d = 1; d < 64; d <<= 1) {
         const int t = __shfl_up(incl, d, 64);
         if (lane >= d) incl += t;
       }
-      if (i < n) s_cost[ph][i] = run + incl - v;
+      if (i < n) s_cost[i] = run + incl - v;
       run += __shfl(incl, 63, 64);
     }
-    if (lane == 0) s_nst[ph] = run;
+    if (lane == 0) s_nst = run;
   }
   lds_barrier();
-  int S_ph[2] = {0, 0};
-  for (int ph = 0; ph < nphase; ++ph) S_ph[ph] = s_nst[ph];
-  if (tid < nphase) {
-    if ((S_ph[tid] + kXcd - 1) / kXcd > qcap) misc[4] = 1;  // cannot happen with the host's capacity bound
-    misc[2 + tid] = s_ng[tid];
+  if (tid == 0) {
+    if ((s_nst + kXcd - 1) / kXcd > qcap) misc[4] = 1;  // cannot happen with the host's capacity bound
+    misc[2 + ph] = s_ng;
   }
-  if (wave < nphase * kXcd) {
-    const int ph = wave / kXcd, x = wave % kXcd;
-    const int ng = s_ng[ph], S = S_ph[ph];
-    const int32_t* s_ns = s_cost[ph];
+  {
+    // two wavefronts per queue: both find its entries and their first tiles,
+    // wavefront x writes the records, and each expands every second entry
+    // (the stores of the entries are what takes long: 24 us of the
+    // Qwen2-shaped plan with one wavefront per queue and phase)
+    const int x = wave % kXcd, half = wave / kXcd;
+    const int ng = s_ng, S = s_nst;
+    const int32_t* s_ns = s_cost;
     // super-tile u -> (rank, index within the group)
     auto locate = [&](int u, int* g, int* st) {
       int lo = 0, hi = ng;
@@ -423,7 +444,7 @@ __global__ void __launch_bounds__(1024) plan_kernel(const DevExpert* __restrict_
         const int mid = (lo + hi) >> 1;
         if (s_ns[mid] <= u) lo = mid; else hi = mid;
       }
-      *g = s_order[ph][lo];
+      *g = s_order[lo];
       *st = u - s_ns[lo];
     };
     int32_t* ent = plan + PL.ent + (int64_t)ph * kXcd * qcap * 3;
@@ -456,9 +477,11 @@ __global__ void __launch_bounds__(1024) plan_kernel(const DevExpert* __restrict_
       // this lane's entry: its record, and what expanding it takes
       int w0 = 0, off_e = 0, m_g = 0, mi0 = 0, ni0 = 0, em = 1, inv = 65536, size = 0;
       if (i < n) {
-        q[(int64_t)i * 3 + 0] = g;
-        q[(int64_t)i * 3 + 1] = st;
-        q[(int64_t)i * 3 + 2] = first;
+        if (half == 0) {
+          q[(int64_t)i * 3 + 0] = g;
+          q[(int64_t)i * 3 + 1] = st;
+          q[(int64_t)i * 3 + 2] = first;
+        }
         if (first + v <= fcap) {
           const SuperDims dd = plan_super_dims(mt, ntv);
           const int sni = div_small(st, dd.nsm), smi = st - sni * dd.nsm;
@@ -466,7 +489,7 @@ __global__ void __launch_bounds__(1024) plan_kernel(const DevExpert* __restrict_
           inv = div_small(65536 + em - 1, em);  // t / em = (t * inv) >> 16 for t < 64, em <= 8
           mi0 = smi * dd.sm;
           ni0 = sni * dd.sn;
-          w0 = tile_word0(g, pick_cfg(s_m[g], s_kd[ph][g], raw_m >= 0 ? 0 : ph), s_kd[ph][g], s_sp[ph][g]);
+          w0 = tile_word0(g, pick_cfg(s_m[g], s_kd[g], raw_m >= 0 ? 0 : ph), s_kd[g], s_sp[g]);
           off_e = s_off[g];
           m_g = s_m[g];
           size = v;
@@ -479,7 +502,7 @@ __global__ void __launch_bounds__(1024) plan_kernel(const DevExpert* __restrict_
       // order of the SuperDims geometry), so that every store is contiguous; the
       // entry's fields come from its lane's registers.
       const int cnt = n - c0 < 64 ? n - c0 : 64;
-      for (int j = 0; j < cnt; ++j) {
+      for (int j = half; j < cnt; j += 2) {
         const int sz = __builtin_amdgcn_readlane(size, j);
         if (sz == 0) continue;
         const int fj = __builtin_amdgcn_readlane(first, j);
@@ -494,7 +517,7 @@ __global__ void __launch_bounds__(1024) plan_kernel(const DevExpert* __restrict_
         }
       }
     }
-    if (lane == 0) {
+    if (lane == 0 && half == 0) {
       ctr[x * 4 + 0] = 0;
       ctr[x * 4 + 1] = run;
       ctr[x * 4 + 2] = n;
@@ -558,7 +581,7 @@ void tile_costs_get(TileCosts* out) {
   *out = g_costs;
 }
 
-hipError_t launch_plan(const DevExpert* experts, int E, int G, int T, const int32_t* counts,
+hipError_t launch_plan(const DevExpert* experts, int E, int G, int T, const RouteJob* job, const int32_t* counts,
                        const int32_t* offsets, int raw_m, const DevLinear& raw_lin, const uint32_t* mask_words,
                        int32_t* plan, int qcap, int fcap, int64_t pfloats, int32_t* down_qmax, int nwg, bool narrow,
                        const XPrep& xp, hipStream_t s) {
@@ -570,8 +593,22 @@ hipError_t launch_plan(const DevExpert* experts, int E, int G, int T, const int3
   nxb = nxb < 1024 ? nxb : 1024;
   TileCosts tc;
   tile_costs_get(&tc);
-  hipLaunchKernelGGL(plan_kernel, dim3(1 + nxb), dim3(1024), 0, s, experts, E, G, T, counts, offsets, raw_m, raw_lin,
-                     mb, plan, qcap, fcap, pfloats, down_qmax, nwg < 1 ? 1 : nwg, narrow ? 4 : 1, xp, tc);
+  const int nplan = raw_m >= 0 ? 1 : 2;
+  nwg = nwg < 1 ? 1 : nwg;
+  const int nsub = narrow ? 4 : 1;
+  RouteJob none;
+  memset(&none, 0, sizeof(none));
+  if (job) {
+    if (job->P > kRouteSmall || G > kSmallG) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((plan_kernel<kSmallG, true>), dim3(nplan + nxb), dim3(1024), 0, s, *job, experts, E, G, T, counts,
+                       offsets, raw_m, raw_lin, mb, plan, qcap, fcap, pfloats, down_qmax, nwg, nsub, xp, tc);
+  } else if (G <= kSmallG) {
+    hipLaunchKernelGGL((plan_kernel<kSmallG, false>), dim3(nplan + nxb), dim3(1024), 0, s, none, experts, E, G, T, counts,
+                       offsets, raw_m, raw_lin, mb, plan, qcap, fcap, pfloats, down_qmax, nwg, nsub, xp, tc);
+  } else {
+    hipLaunchKernelGGL((plan_kernel<kMaxG, false>), dim3(nplan + nxb), dim3(1024), 0, s, none, experts, E, G, T, counts,
+                       offsets, raw_m, raw_lin, mb, plan, qcap, fcap, pfloats, down_qmax, nwg, nsub, xp, tc);
+  }
   return hipGetLastError();
 }
 

@@ -740,7 +740,10 @@ MXMOE_INL void run_tile(Smem<NAR>& sm, const GemmArgs& a, const DevExpert* ex, i
       src = shared ? m : a.rtok[off_e + m];
       out = shared ? (g - a.E_routed) * a.T + m : off_e + m;
       if constexpr (F8 || F6) sc = ascale[src];
-      else if constexpr (INT && !GSC) sc = shared ? ascale[m] : (KD == K_W8A8 ? a.rxs8 : a.rxs4)[off_e + m];
+      else if constexpr (INT && !GSC) {
+        const float* rs = KD == K_W8A8 ? a.rxs8 : a.rxs4;  // null: no copies per sorted row
+        sc = shared || !rs ? ascale[src] : rs[off_e + m];
+      }
     } else if constexpr (PHASE == 1) {
       src = shared ? (g - a.E_routed) * a.T + m : off_e + m;
       if (shared) {

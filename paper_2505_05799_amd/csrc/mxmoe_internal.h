@@ -309,7 +309,33 @@ struct RowMeta {
   int32_t* rslot;
   float* rgw;
 };
+// Router front-end of T tokens (ids, weights and shared gates out).
+struct RouterArgs {
+  const float* logits;  // [T, E]
+  int k, renorm;
+  const float* shared_logits;  // [T, n_sh] or null
+  int n_sh;
+  int32_t* ids;  // [T, k]
+  float* w;      // [T, k]
+  float* shared_w;
+};
+// groups of 8 lanes take a token where its logits and its choice fit them
+constexpr int kGroupMaxE = 64;
+constexpr int kGroupMaxK = 8;
+__host__ __device__ constexpr bool router_by_group(int E, int k) { return E <= kGroupMaxE && k <= kGroupMaxK; }
+// A small batch's routing, done by one workgroup (route_impl.h).  A step of 1024
+// pairs costs ~1 us: past 4096 pairs the chunked launches win.
+constexpr int kRouteSmall = 4096;
+struct RouteJob {
+  const int32_t* ids;  // [T, k]; unused where the router runs (ra.logits, router_by_group(E, k))
+  int P, E, ebits;
+  int32_t *counts, *offsets, *sorted_pair, *inv, *status;
+  RouterArgs ra;
+  RowMeta rm;
+};
 // rm may be null (routing arrays only).
+RouteJob route_job(const int32_t* ids, int T, int k, int E, int32_t* counts, int32_t* offsets, int32_t* sorted_pair,
+                   int32_t* inv, int32_t* status, const RowMeta* rm);
 hipError_t launch_route(const int32_t* ids, int T, int k, int E, int32_t* counts,
                         int32_t* offsets, int32_t* sorted_pair, int32_t* inv, int32_t* status,
                         int32_t* chunk_counts, int32_t* chunk_bad, const RowMeta* rm, hipStream_t s);
@@ -318,15 +344,6 @@ hipError_t launch_route(const int32_t* ids, int T, int k, int E, int32_t* counts
 constexpr int kRouterMaxK = 64;
 hipError_t launch_router_topk(const float* logits, int T, int E, int k, int renorm, const float* shared_logits,
                               int n_sh, int32_t* ids, float* w, float* shared_w, hipStream_t s);
-// The router front-end followed by routing of the ids it writes: one launch
-// where the batch fits the one-workgroup routing kernel (E <= 64, k <= 8),
-// else the two calls above.  Results equal those of the two calls.
-// (rm->topk_w is ignored: the rows take the router's weights w.)
-hipError_t launch_router_route(const float* logits, int T, int E, int k, int renorm, const float* shared_logits,
-                               int n_sh, int32_t* ids, float* w, float* shared_w, int32_t* counts,
-                               int32_t* offsets, int32_t* sorted_pair, int32_t* inv, int32_t* status,
-                               int32_t* chunk_counts, int32_t* chunk_bad, const RowMeta* rm, hipStream_t s);
-
 // Row sums of each 128-wide block of bf16 rows: out[r][b] = sum of a[r][128b ..
 // 128b + 127] in fp32; cols a multiple of 128, rows 16-byte aligned.
 hipError_t launch_rowsum(const void* a, int rows, int cols, int64_t ld, float* out, hipStream_t s);
@@ -450,7 +467,10 @@ struct XPrep {
 // The same launch encodes xp on its other workgroups (they do not wait for
 // the plan, nor it for them).
 // The plan prices tiles with the process-wide cost table (tile_costs_get).
-hipError_t launch_plan(const DevExpert* experts, int E, int G, int T, const int32_t* counts,
+// job: the routing of a small batch (P <= kRouteSmall, G <= kSmallG), which the
+// plan's workgroups then do first, or null (counts and offsets are there).
+constexpr int kSmallG = 256;
+hipError_t launch_plan(const DevExpert* experts, int E, int G, int T, const RouteJob* job, const int32_t* counts,
                        const int32_t* offsets, int raw_m, const DevLinear& raw_lin, const uint32_t* mask_words,
                        int32_t* plan, int qcap, int fcap, int64_t pfloats, int32_t* down_qmax, int nwg, bool narrow,
                        const XPrep& xp, hipStream_t s);

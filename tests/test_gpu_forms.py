@@ -3,10 +3,13 @@ that launches with few tiles are cut into) against the oracle, at the edges of
 their tiles: rows around 16 / 32 / 64 / 128, channels around the item widths
 (64, 128) and the tile widths (256, 512), reductions with and without slices."""
 
+import numpy as np
 import pytest
 
+from oracle import mxmoe_oracle as O
+from paper_2505_05799_amd import mxmoe as M
 from paper_2505_05799_amd import workloads as W
-from tests.gpuhelp import say
+from tests.gpuhelp import say, torch_mod, upload_inputs
 from tests.stagewise import check_forward
 from tests.test_gpu_forward import run_block
 from tests.test_gpu_kernels import _check_linear, _linear_case
@@ -53,3 +56,32 @@ def test_block_forms(T, mix, act):
     mb, y = run_block(blk)
     rep = check_forward(mb, blk, y)
     say(f"T={T} mix {mix} {act}: {rep.line()}")
+
+
+@pytest.mark.parametrize("E,k,T", [(60, 4, 1), (60, 4, 1024), (61, 8, 129), (70, 4, 40), (60, 9, 40), (252, 3, 50), (260, 3, 50)])
+def test_routing_forms(E, k, T):
+    """Routing inside the plan launch (at most 4096 pairs and 256 groups), with
+    the router (at most 64 experts, k <= 8) and without, and in launches of its
+    own: from logits and from the ids and weights they give, the same bits; the
+    routing arrays and the block against the oracle."""
+    torch = torch_mod()
+    blk = W.random_small_block(5 + E + k, T=T, H=128, F=128, E=E, k=k, n_shared=1, F_shared=128, act="bf16",
+                               schemes=[(s,) * 3 for s in (W.W8A8, W.W4A4, W.W4G128, W.FP8)] * (E // 4) +
+                               [(W.W8A8,) * 3] * (E % 4 + 1))
+    logits, _ = W.router_logits(T, E, seed=E, zipf_s=1.0)
+    blk.topk_ids, blk.topk_w = O.router_topk(logits, k)
+    blk.topk_ids = np.ascontiguousarray(blk.topk_ids, dtype=np.int32)
+    mb = M.MoEBlock(blk)
+    x, ids, _ = upload_inputs(blk)
+    lg = torch.from_numpy(logits).cuda()
+    gids, gw, _ = M.router_topk(lg, k)
+    assert torch.equal(gids, ids)
+    y1 = mb.forward(x, None, None, router_logits=lg).clone()
+    y2 = mb.forward(x, gids, gw)
+    torch.cuda.synchronize()
+    assert torch.equal(y1.view(torch.int16), y2.view(torch.int16))
+    r = O.route(blk.topk_ids, E)
+    for f, n in (("counts", E), ("offsets", E + 1), ("sorted_pair", T * k), ("inv", T * k)):
+        assert np.array_equal(mb.ws_view(f, torch.int32, n, T).cpu().numpy(), r[f]), f
+    blk.topk_w = gw.cpu().numpy()
+    say(f"E={E} k={k} T={T}: {check_forward(mb, blk, y2).line()}")
