@@ -162,7 +162,7 @@ bool narrow_block(const BlockInfo& bi, int64_t T) {
   return down <= kNarrowTiles && narrow_launch(up, wr / bi.E * live + ws);
 }
 
-WsLayout layout_of(const BlockInfo& bi, int T) {
+WsLayout layout_of(const BlockInfo& bi, int T, int64_t pmin = kPartialMin) {
   WsLayout L;
   size_t o = 0;
   auto take = [&](size_t bytes) {
@@ -188,9 +188,11 @@ WsLayout layout_of(const BlockInfo& bi, int T) {
   L.rgw = take(4 * P);
   L.rxs8 = bi.any_x8 ? take(4 * P) : kNone;
   L.rxs4 = bi.any_x4 ? take(4 * P) : kNone;
-  // split-K partial sums: a few times the largest layer output, at most 512 MB
+  // split-K partial sums: a few times the largest layer output, at least pmin
+  // (small batches: a slice holds whole tiles, however few of their rows are
+  // the group's), at most 512 MB
   L.pfloats = std::min<int64_t>((int64_t)1 << 27,
-                                4 * ((int64_t)P + (int64_t)bi.nsh * T) * std::max(std::max(bi.F, bi.Fsh), bi.H));
+                                std::max(pmin, 4 * ((int64_t)P + (int64_t)bi.nsh * T) * std::max(std::max(bi.F, bi.Fsh), bi.H)));
   L.partial = take(4 * (size_t)L.pfloats);
   L.xq8 = L.xs8 = L.xq4 = L.xs4 = kNone;
   if (bi.any_x8) { L.xq8 = take((size_t)T * bi.H); L.xs8 = take(4 * (size_t)T); }
@@ -553,9 +555,11 @@ mxmoe_status mxmoe_workspace_layout(const mxmoe_block* B, int32_t T, mxmoe_ws_la
   return MXMOE_OK;
 }
 
-mxmoe_status mxmoe_moe_forward_ex(const mxmoe_block* B, const void* block_table, int32_t T, const void* x,
-                                  const int32_t* topk_ids, const float* topk_w, void* y, void* workspace,
-                                  size_t workspace_bytes, const mxmoe_forward_opts* opts, hipStream_t stream) {
+// pmin: see layout_of
+static mxmoe_status forward_impl(const mxmoe_block* B, const void* block_table, int32_t T, const void* x,
+                                 const int32_t* topk_ids, const float* topk_w, void* y, void* workspace,
+                                 size_t workspace_bytes, const mxmoe_forward_opts* opts, hipStream_t stream,
+                                 int64_t pmin) {
   static thread_local BlockInfo bi;
   mxmoe_status st = check_block(B, &bi);
   if (st != MXMOE_OK) return st;
@@ -580,7 +584,7 @@ mxmoe_status mxmoe_moe_forward_ex(const mxmoe_block* B, const void* block_table,
   if (!aligned(block_table, 16) || !aligned(x, 16) || !aligned(y, 16) || !aligned(workspace, 256) ||
       !aligned(topk_ids, 4) || !aligned(topk_w, 4))
     return MXMOE_ERR_INVALID_ARG;
-  const WsLayout L = layout_of(bi, T);
+  const WsLayout L = layout_of(bi, T, pmin);
   if (workspace_bytes < L.total) return MXMOE_ERR_WORKSPACE;
 
   uint32_t mask_words[64];
@@ -790,6 +794,12 @@ mxmoe_status mxmoe_moe_forward_ex(const mxmoe_block* B, const void* block_table,
   return MXMOE_OK;
 }
 
+mxmoe_status mxmoe_moe_forward_ex(const mxmoe_block* B, const void* block_table, int32_t T, const void* x,
+                                  const int32_t* topk_ids, const float* topk_w, void* y, void* workspace,
+                                  size_t workspace_bytes, const mxmoe_forward_opts* opts, hipStream_t stream) {
+  return forward_impl(B, block_table, T, x, topk_ids, topk_w, y, workspace, workspace_bytes, opts, stream, kPartialMin);
+}
+
 }  // extern "C"
 
 namespace {
@@ -822,13 +832,17 @@ mxmoe_status mxmoe_moe_forward_noalloc(const mxmoe_block* B, const void* block_t
   if (st != MXMOE_OK) return st;
   if (T < 0) return MXMOE_ERR_INVALID_ARG;
   if ((int64_t)T * bi.k >= (1LL << 31)) return MXMOE_ERR_UNSUPPORTED;
-  if (layout_of(bi, T).total > (size_t)MXMOE_NOALLOC_SCRATCH_BYTES) return MXMOE_ERR_WORKSPACE;
+  // the scratch array holds every batch that its size admits without the
+  // partial buffer's lower bound; that bound applies where it still fits
+  int64_t pmin = kPartialMin;
+  if (layout_of(bi, T, pmin).total > (size_t)MXMOE_NOALLOC_SCRATCH_BYTES) pmin = 0;
+  if (layout_of(bi, T, pmin).total > (size_t)MXMOE_NOALLOC_SCRATCH_BYTES) return MXMOE_ERR_WORKSPACE;
   if (T == 0) return MXMOE_OK;
   void* ws = nullptr;
   st = scratch_of_current_device(&ws);
   if (st != MXMOE_OK) return st;
-  return mxmoe_moe_forward_ex(B, block_table, T, x, topk_ids, topk_w, y, ws, (size_t)MXMOE_NOALLOC_SCRATCH_BYTES,
-                              nullptr, stream);
+  return forward_impl(B, block_table, T, x, topk_ids, topk_w, y, ws, (size_t)MXMOE_NOALLOC_SCRATCH_BYTES, nullptr,
+                      stream, pmin);
 }
 
 mxmoe_status mxmoe_moe_forward(const mxmoe_block* B, const void* block_table, int32_t T, const void* x,

@@ -197,13 +197,14 @@ __global__ void __launch_bounds__(1024) plan_kernel(RouteJob job, const DevExper
   // The slice rule (kSplitShare, kSplitMinKb), evaluated by eight lanes per group: lane
   // j prices j + 1 slices; the group takes the fewest slices whose tile cost
   // is within theta, else the cheapest (the fewest slices among equals).
+  const int min_kb = nsub == 1 ? kSplitMinKb : (raw_m >= 0 ? kSplitMinKbNarrowLin : kSplitMinKbNarrow);
   for (int base = 0; base < G; base += (int)blockDim.x / 8) {
     const int item = base + tid / 8, s = (tid & 7) + 1;
     const bool live = item < G;
     const int g = live ? item : 0;
     const Geom q = geom(ph, g);
     const bool tiled = live && q.mt * q.nt > 0;
-    int smax = q.kb / kSplitMinKb;
+    int smax = q.kb / min_kb;
     smax = smax < 1 ? 1 : (smax > kSplitMax ? kSplitMax : smax);
     const bool ok = tiled && s <= smax;
     int32_t c = 0;

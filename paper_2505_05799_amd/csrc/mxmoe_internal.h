@@ -145,6 +145,12 @@ enum PlanField : int32_t {
 constexpr int kSplitExtra = 16384;
 constexpr int kSplitMax = 8;
 
+// Least size of the partial buffer in floats (32 MB).  Sized by the layer's
+// output alone, the buffer of a small batch held the slices of its first
+// groups only: of the Mixtral-shaped block at 32 tokens, half of the down
+// projections (112 k blocks each) ran unsliced and kept the launch going.
+constexpr int64_t kPartialMin = (int64_t)1 << 23;
+
 // Limits of a block: routed experts, shared experts, groups (routed + shared).
 constexpr int kMaxE = 1024;
 constexpr int kMaxShared = 64;
@@ -250,6 +256,13 @@ __host__ __device__ inline int32_t tile_cost(const int32_t* e, int kb, int split
 // 12% slower).
 constexpr int kSplitShare = 2;
 constexpr int kSplitMinKb = 6;
+// Narrow launches: at least 12 k blocks per slice, 8 in a single linear.  A
+// narrow item streams four k blocks per memory round trip (about 1 us) and a
+// hand-off costs three to four, so slices of 6 lose.  6 -> 12: one token of the
+// Qwen1.5-shaped block 56.6 -> 54.1 us, 21 tokens 68.8 -> 64.1; 6 -> 8: a
+// 31-row w4g128 linear of 14336 x 4096 33.2 -> 31.0 us (12: 32.4).
+constexpr int kSplitMinKbNarrow = 12;
+constexpr int kSplitMinKbNarrowLin = 8;
 
 // Workspace layout (byte offsets), shared by host code of the forward.
 struct WsLayout {
