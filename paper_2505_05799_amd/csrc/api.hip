@@ -429,37 +429,35 @@ mxmoe_status mxmoe_linear_forward(const mxmoe_linear* L, mxmoe_dtype act, const 
   ga.qcap = w.qcap;
   ga.fcap = w.fcap;
   ga.partial = at<float>(workspace, w.partial);
+  // the input's encoding rides on the plan launch (its spare workgroups)
+  const bool narrow = narrow_launch(tiles_bound(1, m, L->n, 256), codes_bytes(kd, L->n, L->k));
+  XPrep xp;
+  memset(&xp, 0, sizeof(xp));
+  xp.x = a;
+  xp.act = act;
+  xp.cols = L->k;
   if (kind_is_int(kd)) {
     int8_t* aq = at<int8_t>(workspace, w.aq);
     float* as = at<float>(workspace, w.as);
-    hipError_t e = kd == K_W4A4G ? launch_act_quant_g128(a, act, m, L->k, L->k, kind_qmax(kd), aq, as, stream)
-                   : (kd == K_W4A4F6 ? launch_act_quant_f6(a, act, m, L->k, L->k, reinterpret_cast<uint8_t*>(aq), as, stream)
-                                     : launch_act_quant(a, act, m, L->k, L->k, kind_qmax(kd), aq, as, stream));
-    if (e != hipSuccess) return MXMOE_ERR_HIP;
-    if (kd == K_W8A8) { ga.xq8 = aq; ga.xs8 = as; }
-    else if (kd == K_F8A8) { ga.xqf8 = reinterpret_cast<const uint8_t*>(aq); ga.xsf8 = as; }
-    else if (kd == K_W4A4F6) { ga.xqf6 = reinterpret_cast<const uint8_t*>(aq); ga.xsf6 = as; }
-    else if (kd == K_W4A4G) { ga.xq4g = aq; ga.xs4g = as; }
-    else { ga.xq4 = aq; ga.xs4 = as; }
+    if (kd == K_W8A8) { ga.xq8 = xp.q8 = aq; ga.xs8 = xp.s8 = as; }
+    else if (kd == K_F8A8) { ga.xqf8 = xp.qf8 = reinterpret_cast<uint8_t*>(aq); ga.xsf8 = xp.sf8 = as; }
+    else if (kd == K_W4A4F6) { ga.xqf6 = xp.qf6 = reinterpret_cast<uint8_t*>(aq); ga.xsf6 = xp.sf6 = as; }
+    else if (kd == K_W4A4G) { ga.xq4g = xp.q4g = aq; ga.xs4g = xp.s4g = as; }
+    else { ga.xq4 = xp.q4 = aq; ga.xs4 = xp.s4 = as; }
+    xp.rows = m;
   }
   if (kind_is_mx(kd)) {
-    uint8_t* aq = at<uint8_t>(workspace, w.aq);
-    uint8_t* ae = at<uint8_t>(workspace, w.as);
-    if (launch_act_quant_mx(a, act, m, L->k, L->k, aq, ae, stream) != hipSuccess) return MXMOE_ERR_HIP;
-    ga.xqmx = aq;
-    ga.xsmx = ae;
+    ga.xqmx = xp.qmx = at<uint8_t>(workspace, w.aq);
+    ga.xsmx = xp.smx = at<uint8_t>(workspace, w.as);
+    xp.rows = m;
   }
-  if (act == MXMOE_BF16 && kind_is_magic(kd)) {
-    float* rs = at<float>(workspace, w.rsa);
-    if (launch_rowsum(a, m, L->k, L->k, rs, stream) != hipSuccess) return MXMOE_ERR_HIP;
-    ga.rsx = rs;
+  if (act == MXMOE_BF16 && kind_is_magic(kd) && !narrow) {  // (the narrow form sums the rows itself)
+    ga.rsx = xp.rs = at<float>(workspace, w.rsa);
+    xp.rows = m;
   }
   const int grid = group_gemm_grid(current_device());
-  XPrep nox;
-  memset(&nox, 0, sizeof(nox));
-  const bool narrow = narrow_launch(tiles_bound(1, m, L->n, 256), codes_bytes(kd, L->n, L->k));
   hipError_t e = launch_plan(nullptr, 1, 1, m, nullptr, nullptr, nullptr, m, dl, nullptr, ga.plan, w.qcap, w.fcap, w.pfloats,
-                             nullptr, grid, narrow, nox, stream);
+                             nullptr, grid, narrow, xp, stream);
   if (e != hipSuccess) return MXMOE_ERR_HIP;
   return hip_status(launch_group_gemm(ga, 2, grid, narrow, stream));
 }
