@@ -461,17 +461,28 @@ MXMOE_INL const uint8_t* uniform_ptr(const uint8_t* p) {
   const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
   return reinterpret_cast<const uint8_t*>(((uint64_t)hi << 32) | lo);
 }
+// A scalar register that readfirstlane (a vector instruction) wrote may be read
+// by a vector-memory instruction five wait states later at the earliest; the
+// compiler keeps that distance for its own instructions but does not look into
+// the asm, so the forms that pass the base through readfirstlane wait there
+// (s_mov and s_nop 4: six).
 template <bool UP = false> MXMOE_INL void lds_dma16(const uint8_t* base, uint32_t voff, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-               :
-               : "v"(voff), "s"(UP ? uniform_ptr(base) : base), "s"(lds_addr)
-               : "memory", "m0");
+  if constexpr (UP)
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %0, %1"
+                 :
+                 : "v"(voff), "s"(uniform_ptr(base)), "s"(lds_addr)
+                 : "memory", "m0");
+  else
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                 :
+                 : "v"(voff), "s"(base), "s"(lds_addr)
+                 : "memory", "m0");
 }
 
 // The same load with device scope (sc1: past this XCD's L2), for partial sums
 // that other XCDs stored with store_coherent (base made wave-uniform).
 MXMOE_INL void lds_dma16_coherent(const uint8_t* base, uint32_t voff, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 sc1"
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %0, %1 sc1"
                :
                : "v"(voff), "s"(uniform_ptr(base)), "s"(lds_addr)
                : "memory", "m0");
@@ -563,10 +574,16 @@ template <int RB, class SM> MXMOE_INL u32x4 act_frag(const SM& sm, int buf, int 
 // rows 64w .. 64w + 63 of k block kb into sm.rsum[buf] (wavefronts
 // w < ceil(BM / 64)); rsoff: the lane's row offset (bytes) at k block 0.
 template <bool UP = false> MXMOE_INL void lds_dma4(const uint8_t* base, uint32_t voff, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1"
-               :
-               : "v"(voff), "s"(UP ? uniform_ptr(base) : base), "s"(lds_addr)
-               : "memory", "m0");
+  if constexpr (UP)
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 4\n\tglobal_load_lds_dword %0, %1"
+                 :
+                 : "v"(voff), "s"(uniform_ptr(base)), "s"(lds_addr)
+                 : "memory", "m0");
+  else
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1"
+                 :
+                 : "v"(voff), "s"(base), "s"(lds_addr)
+                 : "memory", "m0");
 }
 // (sub-stage s of a tile of at most RSS rows takes rsum[buf][RSS s ..])
 template <int BM, bool UP, int RSS, class SM>
