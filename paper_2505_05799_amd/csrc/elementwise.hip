@@ -80,37 +80,20 @@ __global__ void __launch_bounds__(kThreads) act_quant_kernel(const void* a, int 
 // ---- one wavefront per row, 16-byte loads (8 elements per lane and chunk)
 constexpr int kRowsPerBlock = kThreads / 64;
 
-__global__ void __launch_bounds__(kThreads) act_quant_mx_kernel(const void* a, int act, int rows, int cols,
-                                                                int64_t ld, uint8_t* codes, uint8_t* exps) {
-  const int64_t r = (int64_t)blockIdx.x * kRowsPerBlock + (threadIdx.x >> 6);
-  if (r >= rows) return;
-  quant_row_mx(reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(a) + r * ld), cols, act,
-               reinterpret_cast<uint4*>(codes + r * (cols >> 1)), exps + r * (cols >> 5));
-}
-
-__global__ void __launch_bounds__(kThreads) act_quant_g128_kernel(const void* a, int act, int rows, int cols,
-                                                                  int64_t ld, int qmax, int8_t* codes,
-                                                                  float* scales) {
-  const int64_t r = (int64_t)blockIdx.x * kRowsPerBlock + (threadIdx.x >> 6);
-  if (r >= rows) return;
-  quant_row_groups(reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(a) + r * ld), cols, act, qmax,
-                   reinterpret_cast<uint2*>(codes + r * cols), scales + r * (cols >> 7));
-}
-
 // row handled by this thread: W == 1 one per wavefront, W == 4 one per workgroup
 template <int W> __device__ inline int64_t my_row() {
   return W == 1 ? (int64_t)blockIdx.x * kRowsPerBlock + (threadIdx.x >> 6) : (int64_t)blockIdx.x;
 }
 
-template <int NC, int W, bool F6 = false>
+template <int NC, int W>
 __global__ void __launch_bounds__(kThreads) act_quant_vec_kernel(const void* a, int act, int rows, int cols,
                                                                  int64_t ld, int qmax, int8_t* codes,
                                                                  float* scales) {
   __shared__ uint32_t red[kThreads / 64];
   const int64_t r = my_row<W>();
   if (r >= rows) return;
-  quant_row_vec<NC, W, F6>(reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(a) + r * ld), cols, act,
-                           qmax, reinterpret_cast<uint2*>(codes + r * cols), scales + r, red);
+  quant_row_vec<NC, W>(reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(a) + r * ld), cols, act,
+                       qmax, reinterpret_cast<uint2*>(codes + r * cols), scales + r, red);
 }
 
 // Register-resident shapes by row length: (chunks per lane, wavefronts per row).
@@ -133,10 +116,16 @@ __host__ __device__ inline int row_waves(RowShape s) { return s == RS_4x4 || s =
 struct HEnc { uint4* mx; uint8_t* mxe; int8_t* q; float* s; float* sg; };
 template <int NC, int W>
 __device__ __attribute__((always_inline)) inline void hquant_row(const uint4* row, int F, int act, int qm, const HEnc& o, uint32_t* red) {
-  if (qm & kDownQMX) {  // MXFP4 down projection: one wavefront per row
-    if (W == 1 || threadIdx.x < 64) quant_row_mx(row, F, act, o.mx, o.mxe);
-  } else if (qm & kDownQGroup) {  // per-128-group scales: one wavefront per row
-    if (W == 1 || threadIdx.x < 64) quant_row_groups(row, F, act, qm & 0xFF, reinterpret_cast<uint2*>(o.q), o.sg);
+  if (qm & (kDownQMX | kDownQGroup)) {  // MXFP4, or per-128-group scales
+    if constexpr (NC > 0) {
+      RowRegs<NC, W> R;
+      R.load(row, F);
+      if (qm & kDownQMX) regs_mx<NC, W>(R, act, reinterpret_cast<uint32_t*>(o.mx), o.mxe);
+      else regs_groups<NC, W>(R, act, qm & 0xFF, reinterpret_cast<uint2*>(o.q), o.sg);
+    } else {
+      if (qm & kDownQMX) quant_row_mx(row, F, act, o.mx, o.mxe);
+      else quant_row_groups(row, F, act, qm & 0xFF, reinterpret_cast<uint2*>(o.q), o.sg);
+    }
   } else if (qm & kDownQF6) {  // int4 codes as FP6 e2m3 groups
     quant_row_vec<NC, W, true>(row, F, act, 7, reinterpret_cast<uint2*>(o.q), o.s, red);
   } else {
@@ -204,16 +193,6 @@ __global__ void __launch_bounds__(kThreads, MAXNC > 8 ? 3 : 5) hquant_kernel(HQu
   if (qm == 0) return;
   const uint16_t* h = reinterpret_cast<const uint16_t*>(shared ? a.h_shared : a.h) + r * F;
   hquant_any<MAXNC>(sh, reinterpret_cast<const uint4*>(h), F, a.act, qm, o, red);
-}
-
-// Row sums of each 128-wide block of bf16 rows, one wavefront per row: a
-// block is 16 chunks of 8 elements, one per lane of a 16-lane group; each lane
-// adds its 8 values in order, then the group adds its lanes pairwise.
-__global__ void __launch_bounds__(kThreads) rowsum_kernel(const uint16_t* __restrict__ a, int rows, int cols,
-                                                          int64_t ld, float* __restrict__ out) {
-  const int64_t r = (int64_t)blockIdx.x * kRowsPerBlock + (threadIdx.x >> 6);
-  if (r >= rows) return;
-  rowsum_row(reinterpret_cast<const uint4*>(a + r * ld), cols, out + r * (cols >> 7));
 }
 
 // 8 outputs per thread.  SC > 0 slots (compile time): every slot row is
@@ -292,16 +271,7 @@ hipError_t launch_rows(int rows, int cols, hipStream_t s, Args... args) {
   return hipGetLastError();
 }
 template <int NC, int W> struct ActQuantK { static constexpr auto fn = act_quant_vec_kernel<NC, W>; };
-template <int NC, int W> struct ActQuantF6K { static constexpr auto fn = act_quant_vec_kernel<NC, W, true>; };
 }  // namespace
-
-hipError_t launch_rowsum(const void* a, int rows, int cols, int64_t ld, float* out, hipStream_t s) {
-  if (rows <= 0) return hipSuccess;
-  if ((reinterpret_cast<uintptr_t>(a) & 15) || cols % 128 || ld % 8) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(rowsum_kernel, dim3((rows + kRowsPerBlock - 1) / kRowsPerBlock), dim3(kThreads), 0, s,
-                     reinterpret_cast<const uint16_t*>(a), rows, cols, ld, out);
-  return hipGetLastError();
-}
 
 hipError_t launch_act_quant(const void* a, int act, int rows, int cols, int64_t ld, int qmax, int8_t* codes,
                             float* scales, hipStream_t s) {
@@ -313,34 +283,6 @@ hipError_t launch_act_quant(const void* a, int act, int rows, int cols, int64_t 
     return hipGetLastError();
   }
   return launch_rows<ActQuantK>(rows, cols, s, a, act, rows, cols, ld, qmax, codes, scales);
-}
-
-hipError_t launch_act_quant_f6(const void* a, int act, int rows, int cols, int64_t ld, uint8_t* codes, float* scales,
-                               hipStream_t s) {
-  if (rows <= 0) return hipSuccess;
-  if ((reinterpret_cast<uintptr_t>(a) & 15) || (reinterpret_cast<uintptr_t>(codes) & 31) || cols % 128 || ld % 8)
-    return hipErrorInvalidValue;
-  return launch_rows<ActQuantF6K>(rows, cols, s, a, act, rows, cols, ld, 7, reinterpret_cast<int8_t*>(codes), scales);
-}
-
-hipError_t launch_act_quant_g128(const void* a, int act, int rows, int cols, int64_t ld, int qmax, int8_t* codes,
-                                 float* scales, hipStream_t s) {
-  if (rows <= 0) return hipSuccess;
-  if ((reinterpret_cast<uintptr_t>(a) & 15) || (reinterpret_cast<uintptr_t>(codes) & 7) || cols % 128 || ld % 8)
-    return hipErrorInvalidValue;
-  hipLaunchKernelGGL(act_quant_g128_kernel, dim3((rows + kRowsPerBlock - 1) / kRowsPerBlock), dim3(kThreads), 0, s, a,
-                     act, rows, cols, ld, qmax, codes, scales);
-  return hipGetLastError();
-}
-
-hipError_t launch_act_quant_mx(const void* a, int act, int rows, int cols, int64_t ld, uint8_t* codes, uint8_t* exps,
-                               hipStream_t s) {
-  if (rows <= 0) return hipSuccess;
-  if ((reinterpret_cast<uintptr_t>(a) & 15) || (reinterpret_cast<uintptr_t>(codes) & 15) || cols % 128 || ld % 8)
-    return hipErrorInvalidValue;
-  hipLaunchKernelGGL(act_quant_mx_kernel, dim3((rows + kRowsPerBlock - 1) / kRowsPerBlock), dim3(kThreads), 0, s, a,
-                     act, rows, cols, ld, codes, exps);
-  return hipGetLastError();
 }
 
 hipError_t launch_hquant(const HQuantArgs& a, bool routed, bool shared, hipStream_t s) {

@@ -357,13 +357,6 @@ hipError_t launch_route(const int32_t* ids, int T, int k, int E, int32_t* counts
 constexpr int kRouterMaxK = 64;
 hipError_t launch_router_topk(const float* logits, int T, int E, int k, int renorm, const float* shared_logits,
                               int n_sh, int32_t* ids, float* w, float* shared_w, hipStream_t s);
-// Row sums of each 128-wide block of bf16 rows: out[r][b] = sum of a[r][128b ..
-// 128b + 127] in fp32; cols a multiple of 128, rows 16-byte aligned.
-hipError_t launch_rowsum(const void* a, int rows, int cols, int64_t ld, float* out, hipStream_t s);
-// Per-(row, 128-wide block) quantization (w4a4-g128 activations): codes int8
-// [rows, cols], scales fp32 [rows][cols/128]; cols a multiple of 128.
-hipError_t launch_act_quant_g128(const void* a, int act, int rows, int cols, int64_t ld, int qmax, int8_t* codes,
-                                 float* scales, hipStream_t s);
 hipError_t launch_act_quant(const void* a, int act, int rows, int cols, int64_t ld, int qmax,
                             int8_t* codes, float* scales, hipStream_t s);
 
@@ -387,16 +380,6 @@ struct HQuantArgs {
   int8_t* hq_shared; float* hs_shared; float* hsg_shared; uint8_t* hqmx_shared; uint8_t* hsmx_shared;
 };
 hipError_t launch_hquant(const HQuantArgs& a, bool routed, bool shared, hipStream_t s);
-// MXFP4 encoding of rows (cols a multiple of 128): codes [rows][cols/2] (two
-// e2m1 nibbles a byte, element order), E8M0 bytes [rows][cols/32].
-hipError_t launch_act_quant_mx(const void* a, int act, int rows, int cols, int64_t ld, uint8_t* codes, uint8_t* exps,
-                               hipStream_t s);
-// Per-row int4 quantization (qmax 7, the per-token recipe) written as FP6 e2m3
-// groups: per 32 elements 24 bytes of 6-bit codes and 8 zero bytes, codes
-// [rows, cols] bytes, scales [rows]; cols a multiple of 128.
-hipError_t launch_act_quant_f6(const void* a, int act, int rows, int cols, int64_t ld, uint8_t* codes, float* scales,
-                               hipStream_t s);
-
 struct GemmArgs {
   const DevExpert* experts;  // device [G]
   int32_t* plan;             // device plan region

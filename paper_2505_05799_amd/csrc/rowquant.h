@@ -269,6 +269,75 @@ __device__ inline void rowsum_row(const uint4* __restrict__ row, int cols, float
   }
 }
 
+// ---- The block-wise encodings of a row held in registers: chunk i of a thread
+// is elements 8 c .. 8 c + 7 with c = idx + kStride i (zeros past the row), all
+// chunks in flight; the blocks' maxima come from shuffles inside the 16
+// (128-wide blocks) or 4 lanes (32-wide) that hold them.
+template <int NC, int W> struct RowRegs {
+  static constexpr int kStride = 64 * W;
+  uint4 v[NC];
+  int idx, nch;
+  __device__ __attribute__((always_inline)) inline void load(const uint4* __restrict__ row, int cols) {
+    idx = W == 1 ? (threadIdx.x & 63) : threadIdx.x;
+    nch = cols >> 3;
+#pragma unroll
+    for (int i = 0; i < NC; ++i) v[i] = has(i) ? row[chunk(i)] : make_uint4(0u, 0u, 0u, 0u);
+  }
+  __device__ __attribute__((always_inline)) inline int chunk(int i) const { return idx + kStride * i; }
+  __device__ __attribute__((always_inline)) inline bool has(int i) const { return chunk(i) < nch; }
+};
+// (a row's chunks are a multiple of 16, so the lanes of a block leave together)
+template <int NC, int W>
+__device__ __attribute__((always_inline)) inline void regs_groups(const RowRegs<NC, W>& R, int act, int qmax,
+                                                                  uint2* __restrict__ codes, float* __restrict__ scales) {
+  const uint32_t nan_lo = act == MXMOE_BF16 ? 0x7f81u : 0x7c01u;
+  const float q = (float)qmax;
+#pragma unroll
+  for (int i = 0; i < NC; ++i) {
+    if (R.has(i)) {
+    uint32_t mb = amax8_bits(R.v[i], nan_lo);
+    for (int d = 1; d < 16; d <<= 1) mb = max(mb, (uint32_t)__shfl_xor((int)mb, d, 64));
+    const float amax = bits_to_f32(mb, act);
+    float inv = 0.f, sc = 0.f;
+    if (amax > 0.f) {
+      inv = __fdiv_rn(q, amax);
+      sc = __fdiv_rn(amax, q);
+    }
+    const int c = R.chunk(i);
+    codes[c] = codes8(R.v[i], act, inv, q);
+    if ((c & 15) == 0) scales[c >> 4] = sc;
+    }
+  }
+}
+template <int NC, int W>
+__device__ __attribute__((always_inline)) inline void regs_mx(const RowRegs<NC, W>& R, int act, uint32_t* __restrict__ codes,
+                                                              uint8_t* __restrict__ exps) {
+  const uint32_t nan_lo = act == MXMOE_BF16 ? 0x7f81u : 0x7c01u;
+#pragma unroll
+  for (int i = 0; i < NC; ++i) {
+    if (R.has(i)) {
+    uint32_t mb = amax8_bits(R.v[i], nan_lo);
+    mb = max(mb, (uint32_t)__shfl_xor((int)mb, 1, 64));
+    mb = max(mb, (uint32_t)__shfl_xor((int)mb, 2, 64));
+    const float amax = bits_to_f32(mb, act);
+    int e = amax > 0.f ? (int)((__float_as_uint(amax) >> 23) & 0xFFu) - 127 - 2 : -127;
+    e = e < -127 ? -127 : (e > 127 ? 127 : e);
+    const float inv = __builtin_amdgcn_ldexpf(1.0f, -e);
+    float f[8];
+    unpack8(R.v[i], act, f);
+    uint32_t o = 0u;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      uint32_t m = e2m1_mag(fabsf(f[j]) * inv);
+      if (f[j] < 0.f && m) m |= 8u;
+      o |= m << (4 * j);
+    }
+    const int c = R.chunk(i);
+    codes[c] = o;
+    if ((c & 3) == 0) exps[c >> 2] = (uint8_t)(e + 127);
+    }
+  }
+}
 // Every encoding of x row r that the block's gate/up linears read (one
 // wavefront; the same recipes as the separate row kernels).
 __device__ inline void x_prep_row(const XPrep& p, int64_t r) {
