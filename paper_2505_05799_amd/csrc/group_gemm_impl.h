@@ -201,9 +201,11 @@ template <int KD> MXMOE_INL void load_raw(Raw<KD>& r, const uint8_t* p) {
     r.d[0] = gload<u32x4>(p);
   }
 }
-// loads of a fragment's k block
+// Load instructions of a fragment's k block, at least: adjacent loads count as
+// one where the compiler may merge them (K_W3G's three dwords become a 12-byte
+// load; 16-byte loads are the widest and stay as they are).
 template <int KD> constexpr int raw_loads() {
-  return KD == K_W16 ? 4 : (KD == K_W3G ? 3 : ((KD == K_W8A8 || KD == K_F8A8 || KD == K_W4A4F6 || KD == K_W8G) ? 2 : 1));
+  return KD == K_W16 ? 4 : ((KD == K_W8A8 || KD == K_F8A8 || KD == K_W4A4F6 || KD == K_W8G) ? 2 : 1);
 }
 
 // streamed kinds: the lane's bytes of MFMA step j
@@ -846,14 +848,14 @@ MXMOE_INL void run_tile(Smem<NAR>& sm, const GemmArgs& a, const DevExpert* ex, i
 #pragma unroll
       for (int mf = 0; mf < MF; ++mf) acc[l][nf][mf] = AccT{0, 0, 0, 0};
 
-  // Vector-memory loads issued after the activation stage (and its row sums) of
-  // the next k block,
-  // at least: one per fragment and step (streamed), one per fragment (group
-  // prefetch; two 16-byte loads for w8a8), plus one metadata dword per fragment
-  // (weight-only).  Waiting for
-  // this many leaves the weight prefetch in flight across the barrier.
+  // Load instructions issued after the activation stage (and its row sums) of
+  // the next k block, at least: one per fragment and step (streamed), raw_loads
+  // per fragment (group prefetch), plus one metadata dword per fragment (kinds
+  // with group scales).  Waiting for this many leaves the weight prefetch in
+  // flight across the barrier; a number above the instructions really issued
+  // would let the barrier publish a stage that has not landed.
   constexpr int kLoadsAfterStage =
-      NL * NF * (streamed<KD, NAR>() ? J : (KD == K_W3G && !NAR ? 1 : raw_loads<KD>())) + (GMETA ? NL * NF : 0);
+      NL * NF * (streamed<KD, NAR>() ? J : raw_loads<KD>()) + (GMETA ? NL * NF : 0);
 
   stage_load<RB, BM>(sm, 0, abase, soffs, kb0, wave);
   if constexpr (RSLOAD) rowsum_load<BM, MX || NAR, RSS>(sm, 0, rsbase, rsoff, kb0, wave);
