@@ -385,6 +385,30 @@ LinWs lin_layout(int kd, int m, int n, int k) {
   w.total = o;
   return w;
 }
+// Whether a single linear's input is encoded by a launch of its own, a
+// workgroup per row held in registers, and not by the plan launch, a wavefront
+// per row.  Up to 4096 columns a wavefront holds the row, and a launch costs
+// 4 to 9 us more (m = 1 to 2048).  A longer row it streams twice, 1 KB per
+// round trip, which delays the product the more the longer the row, the dearer
+// the code (FP8, FP6 and MXFP4 codes take several times the instructions of
+// int8) and the more of a workgroup's 16 wavefronts are encoding.  The lines
+// are where both measured the same, by time in the plan over time apart
+// (n = 2048; m = 1 / 16 / 600): int8 at k = 6144 0.85 / 1.01 / 0.99, 12288
+// 0.99 / 1.31 / 1.09; w4a4-g128 at 10240 1.01 / 1.27 / 1.11; FP8 at 4608
+// 0.82 / 1.06 / 1.00, 8192 1.00 / 1.34 / 1.16; FP6 at 4608 0.89 / 1.16 / 1.08,
+// 6144 1.01 / 1.33 / 1.17; MXFP4 at 4608 0.87 / 1.23 / 1.11, 10240 0.99 / 1.50 /
+// 1.24.  At k = 14336, m = 16, n = 4096: fp8 61 -> 37 us, mxfp4 58 -> 35,
+// w8a8 47 -> 35.
+bool encode_apart(int kd, int m, int k) {
+  const bool few = m <= 8;
+  switch (kd) {
+    case K_W4A4F6: return k > (few ? 6016 : 4096);
+    case K_F8A8: return k > (few ? 8064 : 4096);
+    case K_MXFP4: return k > (few ? 10240 : 4096);
+    case K_W4A4G: return k > (few ? 10112 : 6016);
+    default: return k > (few ? 12160 : 6016);
+  }
+}
 }  // namespace
 
 size_t mxmoe_linear_workspace_bytes(const mxmoe_linear* L, int32_t m) {
@@ -429,7 +453,8 @@ mxmoe_status mxmoe_linear_forward(const mxmoe_linear* L, mxmoe_dtype act, const 
   ga.qcap = w.qcap;
   ga.fcap = w.fcap;
   ga.partial = at<float>(workspace, w.partial);
-  // the input's encoding rides on the plan launch (its spare workgroups)
+  // the input's encoding rides on the plan launch (its spare workgroups), or
+  // takes a launch of its own (encode_apart)
   const bool narrow = narrow_launch(tiles_bound(1, m, L->n, 256), codes_bytes(kd, L->n, L->k));
   XPrep xp;
   memset(&xp, 0, sizeof(xp));
@@ -454,6 +479,22 @@ mxmoe_status mxmoe_linear_forward(const mxmoe_linear* L, mxmoe_dtype act, const 
   if (act == MXMOE_BF16 && kind_is_magic(kd) && !narrow) {  // (the narrow form sums the rows itself)
     ga.rsx = xp.rs = at<float>(workspace, w.rsa);
     xp.rows = m;
+  }
+  if (kind_quant_act(kd) && encode_apart(kd, m, L->k)) {
+    HQuantArgs qa;
+    memset(&qa, 0, sizeof(qa));
+    qa.h_shared = a;
+    qa.act = act;
+    qa.T = m;
+    qa.nsh = 1;
+    qa.Fsh = L->k;
+    qa.qm = row_code(kd);
+    qa.hq_shared = at<int8_t>(workspace, w.aq);
+    qa.hs_shared = qa.hsg_shared = at<float>(workspace, w.as);
+    qa.hqmx_shared = at<uint8_t>(workspace, w.aq);
+    qa.hsmx_shared = at<uint8_t>(workspace, w.as);
+    if (launch_hquant(qa, false, true, stream) != hipSuccess) return MXMOE_ERR_HIP;
+    xp.rows = 0;
   }
   const int grid = group_gemm_grid(current_device());
   hipError_t e = launch_plan(nullptr, 1, 1, m, nullptr, nullptr, nullptr, m, dl, nullptr, ga.plan, w.qcap, w.fcap, w.pfloats,

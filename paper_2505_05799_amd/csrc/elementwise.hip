@@ -168,7 +168,7 @@ __global__ void __launch_bounds__(kThreads, MAXNC > 8 ? 3 : 5) hquant_kernel(HQu
   int qm;
   if (shared) {
     if (r >= (int64_t)a.nsh * a.T) return;
-    qm = a.down_qmax[a.E + (int)(r / a.T)];
+    qm = a.down_qmax ? a.down_qmax[a.E + (int)(r / a.T)] : a.qm;
     o.q = a.hq_shared + r * F;
     o.s = a.hs_shared + r;
     o.sg = a.hsg_shared + r * (F >> 7);

@@ -115,12 +115,7 @@ __global__ void __launch_bounds__(1024) plan_kernel(RouteJob job, const DevExper
     s_n[g] = L.n;
     s_kb[g] = L.k / 128;
     s_kd[g] = (int8_t)L.kind;
-    if (raw_m < 0 && ph == 1) {
-      const int dk = L.kind;
-      down_qmax[g] = dk == K_MXFP4 ? kDownQMX
-                    : (dk == K_F8A8 ? kDownQF8
-                                    : (kind_qmax(dk) | (dk == K_W4A4G ? kDownQGroup : 0) | (dk == K_W4A4F6 ? kDownQF6 : 0)));
-    }
+    if (raw_m < 0 && ph == 1) down_qmax[g] = row_code(L.kind);
   }
   if constexpr (ROUTE) {
     int c, f;

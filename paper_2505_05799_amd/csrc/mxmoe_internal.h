@@ -369,13 +369,20 @@ constexpr int kDownQGroup = 0x100;
 constexpr int kDownQMX = 0x200;  // MXFP4 codes into hqmx [P][F/2], E8M0 bytes into hsmx [P][F/32]
 constexpr int kDownQF8 = 0x400;  // FP8 e4m3 codes into hq, per-row scales into hs
 constexpr int kDownQF6 = 0x800;  // int4 codes as FP6 e2m3 (32 per 24 + 8 zero bytes) into hq, scales into hs
+// the encoding that a kind's input rows take (0: none)
+__host__ __device__ constexpr inline int row_code(int kd) {
+  return kd == K_MXFP4 ? kDownQMX
+                       : (kd == K_F8A8 ? kDownQF8
+                                       : (kind_qmax(kd) | (kd == K_W4A4G ? kDownQGroup : 0) | (kd == K_W4A4F6 ? kDownQF6 : 0)));
+}
 // Shared expert j's rows j T .. j T + T - 1 follow down_qmax[E + j] alike, into
 // the shared buffers.
 struct HQuantArgs {
   const void* h; const void* h_shared;
   int act, T, P, F, E, nsh, Fsh;
   const int32_t* offsets;
-  const int32_t* down_qmax;
+  const int32_t* down_qmax;  // null: shared rows only, all of them in encoding qm
+  int qm;
   int8_t* hq; float* hs; float* hsg; uint8_t* hqmx; uint8_t* hsmx;
   int8_t* hq_shared; float* hs_shared; float* hsg_shared; uint8_t* hqmx_shared; uint8_t* hsmx_shared;
 };

@@ -85,3 +85,61 @@ def test_routing_forms(E, k, T):
         assert np.array_equal(mb.ws_view(f, torch.int32, n, T).cpu().numpy(), r[f]), f
     blk.topk_w = gw.cpu().numpy()
     say(f"E={E} k={k} T={T}: {check_forward(mb, blk, y2).line()}")
+
+
+QUANT_ACT = [s for s in W.ALL_SCHEMES if s.a_bits < 16]
+
+
+@pytest.mark.parametrize("scheme", QUANT_ACT, ids=lambda s: s.name)
+@pytest.mark.parametrize("m,n,k", [(8, 48, 4224), (9, 48, 4224), (9, 16, 6144), (8, 16, 6144), (8, 48, 12288),
+                                   (41, 16, 8192), (3, 16, 16512), (2, 16, 32896)])
+def test_linear_long_rows(scheme, m, n, k):
+    """Inputs of more than 4096 columns, on both sides of the lines where their
+    encoding moves from the plan launch to one of its own, and of more columns
+    than a workgroup holds in registers."""
+    for act in ("bf16", "fp16"):
+        q, a, got, _ = _linear_case(scheme, act, m, n, k, m + n + k)
+        _check_linear(q, a, got, act)
+
+
+@pytest.mark.parametrize("scheme", QUANT_ACT, ids=lambda s: s.name)
+def test_long_rows_are_read_in_few_round_trips(scheme):
+    """16 rows of 28672 columns against 14336: the weights of the second half
+    (up to 29 MB) stream in about 10 us.  A wavefront that reads its row in
+    1 KB round trips, twice, adds 56 of them, 28 us and more."""
+    torch = torch_mod()
+
+    def us(k):
+        q = W.QLinear(scheme, 2048, k, *_random_operands(scheme, 2048, k))
+        pl = M.PackedLinear(q, "bf16")
+        a = torch.randn(16, k, device="cuda").bfloat16()
+        for _ in range(3):
+            M.linear_forward(pl, a)
+        best = 1e9
+        for _ in range(8):
+            t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            t0.record()
+            for _ in range(20):
+                M.linear_forward(pl, a)
+            t1.record()
+            t1.synchronize()
+            best = min(best, t0.elapsed_time(t1) * 1e3 / 20)
+        return best
+
+    short, long = us(14336), us(28672)
+    say(f"{scheme.name}: 16 x 14336 {short:.1f} us, 16 x 28672 {long:.1f} us")
+    assert long - short < 20.0
+
+
+def _random_operands(s, n, k):
+    """Codes and scales of the scheme's formats (their values do not matter)."""
+    rng = np.random.default_rng(k)
+    if s.fmt == 1:
+        return rng.integers(0, 16, (n, k), dtype=np.uint8), np.full((n, k // 32), 127, np.uint8)
+    if s.fmt == 2:
+        return rng.integers(0, 0x70, (n, k), dtype=np.uint8), np.full(n, 0.01, np.float32)
+    top = (1 << (s.w_bits - 1)) - 1
+    codes = rng.integers(-top, top + 1, (n, k), dtype=np.int8)
+    if s.w_group > 0:
+        return codes, np.full((n, k // s.w_group), 0.01, np.float16)
+    return codes, np.full(n, 0.01, np.float32)
