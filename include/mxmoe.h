@@ -346,7 +346,9 @@ typedef struct {
                            queue counters [2][8][4], misc [16], the queues
                            expanded to tiles [2][8][plan_flat_cap][4], and
                            split-K arrival counters [2][16384]; misc[8] is
-                           the workgroup count the slicing assumed            */
+                           the workgroup count the slicing assumed, misc[9]
+                           the items a tile is claimed in: 4 in a launch of
+                           the narrow form, else 1                            */
   size_t xq8, xs8;      /* int8 [T,H], fp32 [T]: x codes for a8 gate/up      */
   size_t xq4, xs4;      /* int8 [T,H], fp32 [T]: x codes for a4 gate/up      */
   size_t h;             /* act [T*k, F]: routed h rows, sorted-pair order    */

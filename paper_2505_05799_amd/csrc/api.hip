@@ -144,9 +144,27 @@ bool activations_fit(const BlockInfo& bi, int64_t T) {
 int64_t tiles_bound(int64_t groups, int64_t rows, int n, int bn) {
   return (groups + rows / 64) * ((n + bn - 1) / bn);
 }
+// A launch's tiles and super-tiles as the plan cuts them if the rows are spread
+// evenly; heavy: tiles with those of w4a4-g128 counted half.
+struct TileGuess {
+  int64_t tiles = 0, heavy = 0, supers = 0;
+  void add(int64_t rows, int n, int kd, int bn_phase) {
+    const int c = pick_cfg((int)rows, kd, 0);
+    const int64_t mt = (rows + cfg_bm(c) - 1) / cfg_bm(c), nt = (n + cfg_bn(c, bn_phase) - 1) / cfg_bn(c, bn_phase);
+    const int64_t sm = std::min<int64_t>(mt, 8), sn = std::min(nt, kSuperTiles / sm);
+    tiles += mt * nt;
+    heavy += kd == K_W4A4G ? mt * nt / 2 : mt * nt;
+    supers += ((mt + sm - 1) / sm) * ((nt + sn - 1) / sn);
+  }
+};
 // The narrow form takes launches with few tiles, and those up to kNarrowTiles
-// whose tiles stream many weight bytes.
-bool narrow_launch(int64_t tiles, int64_t weight_bytes) {
+// whose tiles stream many weight bytes, unless the tiles fill the chip as they
+// are (kWideTiles).  rows: of a group, in the mean; kb: k blocks.
+bool narrow_launch(int64_t tiles, int64_t weight_bytes, int64_t rows, int kb, const TileGuess& t) {
+  if (rows > 32) {
+    if (t.heavy >= kWideTiles && t.tiles <= kWideMost && t.supers >= kWideSupers) return false;
+    if (t.tiles >= kWideDeep && t.tiles * kSplitMax <= kWideMost && kb >= kSplitMax * kSplitMinKb) return false;
+  }
   return tiles <= kNarrowFew || (tiles <= kNarrowTiles && weight_bytes >= tiles * kNarrowBytes);
 }
 // Whether the block's Group-GEMM launches take the narrow form (decided on the
@@ -156,10 +174,18 @@ bool narrow_block(const BlockInfo& bi, int64_t T) {
   const int64_t P = T * bi.k, live = std::min<int64_t>(bi.E, P), sh = (int64_t)bi.nsh * T;
   const int64_t up = tiles_bound(live, P, bi.F, 128) + tiles_bound(bi.nsh, sh, bi.Fsh, 128);
   const int64_t down = tiles_bound(live, P, bi.H, 256) + tiles_bound(bi.nsh, sh, bi.H, 256);
+  const int64_t rows = live > 0 ? (P + live - 1) / live : 0;
   int64_t wr = 0, ws = 0;
-  for (int g = 0; g < bi.G; ++g)
-    (g < bi.E ? wr : ws) += 2 * codes_bytes(bi.kinds[g][0], g < bi.E ? bi.F : bi.Fsh, bi.H);
-  return down <= kNarrowTiles && narrow_launch(up, wr / bi.E * live + ws);
+  TileGuess tr, t;
+  for (int g = 0; g < bi.G; ++g) {
+    const bool routed = g < bi.E;
+    (routed ? wr : ws) += 2 * codes_bytes(bi.kinds[g][0], routed ? bi.F : bi.Fsh, bi.H);
+    (routed ? tr : t).add(routed ? rows : T, routed ? bi.F : bi.Fsh, bi.kinds[g][0], 0);
+  }
+  t.tiles += tr.tiles * live / bi.E;
+  t.heavy += tr.heavy * live / bi.E;
+  t.supers += tr.supers * live / bi.E;
+  return down <= kNarrowTiles && narrow_launch(up, wr / bi.E * live + ws, rows, bi.H / 128, t);
 }
 
 WsLayout layout_of(const BlockInfo& bi, int T, int64_t pmin = kPartialMin) {
@@ -455,7 +481,9 @@ mxmoe_status mxmoe_linear_forward(const mxmoe_linear* L, mxmoe_dtype act, const 
   ga.partial = at<float>(workspace, w.partial);
   // the input's encoding rides on the plan launch (its spare workgroups), or
   // takes a launch of its own (encode_apart)
-  const bool narrow = narrow_launch(tiles_bound(1, m, L->n, 256), codes_bytes(kd, L->n, L->k));
+  TileGuess tg;
+  tg.add(m, L->n, kd, 1);
+  const bool narrow = narrow_launch(tiles_bound(1, m, L->n, 256), codes_bytes(kd, L->n, L->k), m, L->k / 128, tg);
   XPrep xp;
   memset(&xp, 0, sizeof(xp));
   xp.x = a;

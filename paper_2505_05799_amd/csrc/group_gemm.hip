@@ -130,6 +130,7 @@ __global__ void __launch_bounds__(1024) plan_kernel(RouteJob job, const DevExper
     if (ph == 0) {
       misc[4] = 0;
       misc[8] = nwg;
+      misc[9] = nsub;
     }
   }
   lds_barrier();

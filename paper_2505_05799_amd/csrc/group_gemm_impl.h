@@ -77,27 +77,7 @@ constexpr int KC = 128;        // k per stage = one weight group
 constexpr int BM_MAX = 128;
 constexpr int STAGE_BYTES = BM_MAX * 256;
 
-// ------------------------------------------------------------ tile configs
-// MF: 16-row fragments per tile (BM = 16 MF); NF: 16-channel fragments per
-// wavefront and linear.  Accumulator registers per lane = 4 * MF * NF * NL.
-__host__ __device__ constexpr int cfg_mf(int c) { return c == CFG_S ? 1 : (c == CFG_T ? 2 : (c == CFG_M ? 4 : 8)); }
-__host__ __device__ constexpr int cfg_nf(int c, int phase) {
-  return phase == 0 ? ((c == CFG_S || c == CFG_T) ? 4 : 2) : ((c == CFG_S || c == CFG_T) ? 8 : 4);
-}
-__host__ __device__ constexpr int cfg_bm(int c) { return 16 * cfg_mf(c); }
-__host__ __device__ constexpr int cfg_bn(int c, int phase) { return 64 * cfg_nf(c, phase); }
-// Tile configuration of a group from its rows; w4a4-g128 and mxfp4 groups stop
-// at 64-row tiles (the per-group rescale keeps a partial sum next to every
-// accumulator; the scaled FP4 MFMA adds its scale registers), and so do fp8
-// groups outside the down phase (its two linears' 32-byte operands do not fit
-// next to 128-row accumulators), which keeps every kernel within its register
-// budget.  phase: 0 gate|up (and single linears), 1 down.
-__host__ MXMOE_INL int pick_cfg(int m, int kind, int phase) {
-  const int c = m <= 16 ? CFG_S : (m <= 32 ? CFG_T : (m <= 64 ? CFG_M : CFG_L));
-  const bool cap = kind == K_W4A4G || kind == K_MXFP4 || (kind == K_F8A8 && phase != 1);
-  return (cap && c == CFG_L) ? CFG_M : c;
-}
-
+// ------------------------------------------------------------ narrow items
 // The narrow form of a launch with few tiles (kNarrowFew, kNarrowTiles): every
 // planned tile is claimed as four items that cut its output, all of them with
 // NF = 1 (gate|up) or 2 (down, single linears) channel fragments per

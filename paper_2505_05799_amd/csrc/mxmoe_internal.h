@@ -128,6 +128,25 @@ struct DevHeader {
 // Tile configurations of the persistent Group-GEMM (16, 32, 64, 128 rows).
 // All use 256 threads (4 wavefronts stacked along the output channels).
 enum Cfg : int32_t { CFG_S = 0, CFG_T = 1, CFG_M = 2, CFG_L = 3, CFG_COUNT = 4 };
+// MF: 16-row fragments per tile (BM = 16 MF); NF: 16-channel fragments per
+// wavefront and linear.  Accumulator registers per lane = 4 * MF * NF * NL.
+__host__ __device__ constexpr int cfg_mf(int c) { return c == CFG_S ? 1 : (c == CFG_T ? 2 : (c == CFG_M ? 4 : 8)); }
+__host__ __device__ constexpr int cfg_nf(int c, int phase) {
+  return phase == 0 ? ((c == CFG_S || c == CFG_T) ? 4 : 2) : ((c == CFG_S || c == CFG_T) ? 8 : 4);
+}
+__host__ __device__ constexpr int cfg_bm(int c) { return 16 * cfg_mf(c); }
+__host__ __device__ constexpr int cfg_bn(int c, int phase) { return 64 * cfg_nf(c, phase); }
+// Tile configuration of a group from its rows; w4a4-g128 and mxfp4 groups stop
+// at 64-row tiles (the per-group rescale keeps a partial sum next to every
+// accumulator; the scaled FP4 MFMA adds its scale registers), and so do fp8
+// groups outside the down phase (its two linears' 32-byte operands do not fit
+// next to 128-row accumulators), which keeps every kernel within its register
+// budget.  phase: 0 gate|up (and single linears), 1 down.
+__host__ __device__ __attribute__((always_inline)) inline int pick_cfg(int m, int kind, int phase) {
+  const int c = m <= 16 ? CFG_S : (m <= 32 ? CFG_T : (m <= 64 ? CFG_M : CFG_L));
+  const bool cap = kind == K_W4A4G || kind == K_MXFP4 || (kind == K_F8A8 && phase != 1);
+  return (cap && c == CFG_L) ? CFG_M : c;
+}
 
 // Plan record per (phase, expert): int32 fields.  A group of mt x nt output
 // tiles whose reduction is sliced S ways (split-K, the paper's slice-K tile
@@ -173,7 +192,9 @@ constexpr int kSuperTiles = 64;
 //   misc  [16]                [2 + p]: number of groups with tiles in phase p,
 //                             [4]: 1 if a queue overflowed its capacity,
 //                             [6 + p]: partial-buffer floats used in phase p,
-//                             [8]: workgroups the slicing threshold assumes
+//                             [8]: workgroups the slicing threshold assumes,
+//                             [9]: items a tile is claimed in (4 in a narrow
+//                             launch, else 1)
 //   flat  [2][kXcd][fcap][4]  the queues expanded to one entry per tile
 //   cnt   [2][kSplitExtra]    arrival counters of sliced output tiles
 struct PlanLayout { int64_t rec, order, ent, ctr, misc, flat, cnt, total; };
@@ -299,6 +320,27 @@ constexpr int64_t kNarrowFew = 512;
 constexpr int64_t kNarrowTiles = 2048;
 constexpr int64_t kNarrowBytes = 192 << 10;
 static_assert(4 * kNarrowTiles <= kSplitExtra, "arrival counters of narrow items");
+// Of those, the launches whose groups have more than 32 rows and whose tiles
+// (estimated from evenly spread rows) fill the chip by themselves stay wide:
+// from kWideTiles to the 512 resident workgroups, in enough super-tiles that
+// every XCD's queue gets its share (with fewer, XCDs idle and the narrow
+// form's even deal wins: a w16 linear of 1984 rows, n = k = 4096, 256 tiles in
+// four super-tiles, 172 -> 118 us narrow).  A narrow item's MFMAs share a weight
+// fragment between half as many rows.  Narrow -> wide: fp8 linears of 1984
+// rows, n = 4096 (496 tiles), k = 4096 85 -> 60 us, k = 14336 312 -> 175; mxfp4
+// 64 -> 47, 202 -> 148; w16, 8000 rows, n = 1024, 124 -> 92; blocks of 16
+// experts of 768, 700 tokens (228 tiles), 162 -> 141 (w16) and 108 -> 92 (fp8);
+// 11 experts of 1280, 2329 tokens, fp8 168 -> 113.  On the other side: 4 experts
+// of 1408, 2500 tokens (220 tiles in four super-tiles), w8a8 90 -> 110; 156
+// tiles (9 experts of 1536, w3g128) 0.7 of the wide time.  A w4a4-g128 tile
+// counts half: its group rescale costs more per row, and at 252 tiles the
+// narrow form still wins (52 against 61 us), at 496 the wide (79 -> 71).
+// A few deep tiles fill the workgroups in kSplitMax slices: w8a8, 512 rows, n =
+// 4096, k = 14336 (64 tiles) 100 -> 91, fp8 of 256 rows 102 -> 89.
+constexpr int64_t kWideTiles = 200;
+constexpr int64_t kWideMost = 512;
+constexpr int64_t kWideSupers = 7;
+constexpr int64_t kWideDeep = 60;  // .. kWideMost / kSplitMax tiles
 
 constexpr int kRouteChunk = 512;  // pairs per routing workgroup
 constexpr size_t kNone = (size_t)-1;

@@ -132,7 +132,7 @@ def test_long_rows_are_read_in_few_round_trips(scheme):
 
 
 def _random_operands(s, n, k):
-    """Codes and scales of the scheme's formats (their values do not matter)."""
+    """Codes and scales of a quantized scheme's formats (their values do not matter)."""
     rng = np.random.default_rng(k)
     if s.fmt == 1:
         return rng.integers(0, 16, (n, k), dtype=np.uint8), np.full((n, k // 32), 127, np.uint8)
@@ -143,3 +143,37 @@ def _random_operands(s, n, k):
     if s.w_group > 0:
         return codes, np.full((n, k // s.w_group), 0.01, np.float16)
     return codes, np.full(n, 0.01, np.float32)
+
+
+def _linear_items(s, m, n, k):
+    """Items a tile of the linear's launch is claimed in (the plan's misc[9])."""
+    torch = torch_mod()
+    pl = M.PackedLinear(W.QLinear(s, n, k, *_random_operands(s, n, k)), "bf16")
+    _, ws = M.linear_forward(pl, torch.zeros(m, k, dtype=torch.bfloat16, device="cuda"), return_ws=True)
+    torch.cuda.synchronize()
+    cap = (m // 1024 + 3) * (n // 512 + 2) // 8 + 2 + 16384 // 8 + 1     # plan_queue_cap
+    at = 28 + 2 * 8 * cap * 3 + 2 * 8 * 4 + 9                            # records, order, entries, counters
+    return int(ws[4 * at: 4 * at + 4].view(torch.int32).item())
+
+
+@pytest.mark.parametrize("scheme,m,n,k,items", [
+    (W.W4A4, 31, 1040, 512, 4), (W.FP8, 1984, 4096, 256, 1), (W.MXFP4, 2021, 3408, 256, 1),
+    (W.FP8, 500, 14336, 128, 1), (W.FP8, 256, 14336, 128, 4), (W.W8A8, 1984, 4096, 256, 4),
+    (W.W8A8, 8000, 1024, 256, 1), (W.W4A4G128, 4000, 1024, 256, 4), (W.W4A4G128, 8000, 1024, 256, 1),
+    (W.W8A8, 512, 4096, 6144, 1), (W.W8A8, 512, 4096, 6016, 4), (W.W8A8, 300, 4096, 6144, 4)],
+    ids=lambda v: getattr(v, "name", str(v)))
+def test_linear_form(scheme, m, n, k, items):
+    """Launches of few tiles are narrow (items 4); those whose tiles fill the
+    chip are not: 200 to 512 tiles in seven super-tiles or more, or 60 to 64
+    of at least 48 k blocks."""
+    assert _linear_items(scheme, m, n, k) == items
+
+
+@pytest.mark.parametrize("T,items", [(2000, 4), (3200, 1)])
+def test_block_form(T, items):
+    """8 experts of 4 channel tiles: 4 row tiles each (128 tiles), or 7 (224)."""
+    from tests.test_gpu_configs import plan_misc
+    blk = W.random_small_block(T, T=T, H=256, F=512, E=8, k=2, act="bf16", schemes=[(W.W8A8,) * 3] * 8)
+    mb, y = run_block(blk)
+    assert plan_misc(mb, T, 8, mb.workspace_layout(T)["plan_queue_cap"])[9] == items
+    say(f"T={T}: {check_forward(mb, blk, y).line()}")
