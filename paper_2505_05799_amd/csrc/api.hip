@@ -414,26 +414,30 @@ LinWs lin_layout(int kd, int m, int n, int k) {
 // Whether a single linear's input is encoded by a launch of its own, a
 // workgroup per row held in registers, and not by the plan launch, a wavefront
 // per row.  Up to 4096 columns a wavefront holds the row, and a launch costs
-// 4 to 9 us more (m = 1 to 2048).  A longer row it streams twice, 1 KB per
-// round trip, which delays the product the more the longer the row, the dearer
-// the code (FP8, FP6 and MXFP4 codes take several times the instructions of
-// int8) and the more of a workgroup's 16 wavefronts are encoding.  The lines
-// are where both measured the same, by time in the plan over time apart
-// (n = 2048; m = 1 / 16 / 600): int8 at k = 6144 0.85 / 1.01 / 0.99, 12288
-// 0.99 / 1.31 / 1.09; w4a4-g128 at 10240 1.01 / 1.27 / 1.11; FP8 at 4608
-// 0.82 / 1.06 / 1.00, 8192 1.00 / 1.34 / 1.16; FP6 at 4608 0.89 / 1.16 / 1.08,
-// 6144 1.01 / 1.33 / 1.17; MXFP4 at 4608 0.87 / 1.23 / 1.11, 10240 0.99 / 1.50 /
-// 1.24.  At k = 14336, m = 16, n = 4096: fp8 61 -> 37 us, mxfp4 58 -> 35,
-// w8a8 47 -> 35.
+// 4 to 9 us more.  A longer row it streams twice, 1 KB per round trip, which
+// delays the product the more the longer the row, the dearer the code (FP8,
+// FP6 and MXFP4 codes take several times the instructions of int8) and the
+// more of a workgroup's 16 wavefronts are encoding; from some 1500 rows on the
+// plan launch has wavefronts on every CU and streams well, until at 4096 rows
+// its workgroups (one per CU) come in turns.  The lines are where both measured
+// the same.  Time in the plan over time apart, at 1 / 16 / 600 rows (n = 2048)
+// and 3072 / 8192 (n = 1024):
+//   int8      k = 6144  0.85 1.01 0.99 0.90 1.07   14336  1.07 1.39 1.12 1.01 1.20
+//   w4a4-g128 k = 6144  0.86 1.07 1.01 0.89 0.99   14336  1.12 1.45 1.15 0.94 1.03
+//   FP8       k = 4608  0.82 1.06 1.00 0.88 1.03    8192  1.00 1.34 1.16 0.99 1.10
+//   FP6       k = 4608  0.89 1.16 1.08 0.94 1.08    6144  1.01 1.33 1.17 1.00 1.14
+//   MXFP4     k = 4608  0.87 1.23 1.11 0.95 1.10   14336  1.09 1.74 1.31 0.95 0.98
+// At 16 rows, n = 4096, k = 14336: fp8 61 -> 37 us, mxfp4 58 -> 35, w8a8 47 -> 35.
 bool encode_apart(int kd, int m, int k) {
-  const bool few = m <= 8;
-  switch (kd) {
-    case K_W4A4F6: return k > (few ? 6016 : 4096);
-    case K_F8A8: return k > (few ? 8064 : 4096);
-    case K_MXFP4: return k > (few ? 10240 : 4096);
-    case K_W4A4G: return k > (few ? 10112 : 6016);
-    default: return k > (few ? 12160 : 6016);
-  }
+  constexpr int never = INT32_MAX;
+  // longest row that stays in the plan: up to 8, 1536, 6000 and more rows
+  constexpr int kInt8[4] = {12160, 6016, 10240, 6016};
+  constexpr int kG128[4] = {10112, 6016, never, 6016};
+  constexpr int kF8[4] = {8064, 4096, 8064, 4096};
+  constexpr int kF6[4] = {6016, 4096, 6016, 4096};
+  constexpr int kMx[4] = {10240, 4096, never, 4096};
+  const int r = m <= 8 ? 0 : (m <= 1536 ? 1 : (m <= 6000 ? 2 : 3));
+  return k > (kd == K_W4A4F6 ? kF6 : kd == K_F8A8 ? kF8 : kd == K_MXFP4 ? kMx : kd == K_W4A4G ? kG128 : kInt8)[r];
 }
 }  // namespace
 

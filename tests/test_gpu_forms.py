@@ -92,7 +92,7 @@ QUANT_ACT = [s for s in W.ALL_SCHEMES if s.a_bits < 16]
 
 @pytest.mark.parametrize("scheme", QUANT_ACT, ids=lambda s: s.name)
 @pytest.mark.parametrize("m,n,k", [(8, 48, 4224), (9, 48, 4224), (9, 16, 6144), (8, 16, 6144), (8, 48, 12288),
-                                   (41, 16, 8192), (3, 16, 16512), (2, 16, 32896)])
+                                   (41, 16, 8192), (1537, 16, 6144), (3, 16, 16512), (2, 16, 32896)])
 def test_linear_long_rows(scheme, m, n, k):
     """Inputs of more than 4096 columns, on both sides of the lines where their
     encoding moves from the plan launch to one of its own, and of more columns
