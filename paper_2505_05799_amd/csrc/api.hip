@@ -163,7 +163,7 @@ struct TileGuess {
 bool narrow_launch(int64_t tiles, int64_t weight_bytes, int64_t rows, int kb, const TileGuess& t) {
   if (rows > 32) {
     if (t.heavy >= kWideTiles && t.tiles <= kWideMost && t.supers >= kWideSupers) return false;
-    if (t.tiles >= kWideDeep && t.tiles * kSplitMax <= kWideMost && kb >= kSplitMax * kSplitMinKb) return false;
+    if (t.tiles >= kWideDeep && t.tiles * kSplitMax <= kWideMost && kb >= kWideDeepKb) return false;
   }
   return tiles <= kNarrowFew || (tiles <= kNarrowTiles && weight_bytes >= tiles * kNarrowBytes);
 }

@@ -336,11 +336,13 @@ static_assert(4 * kNarrowTiles <= kSplitExtra, "arrival counters of narrow items
 // counts half: its group rescale costs more per row, and at 252 tiles the
 // narrow form still wins (52 against 61 us), at 496 the wide (79 -> 71).
 // A few deep tiles fill the workgroups in kSplitMax slices: w8a8, 512 rows, n =
-// 4096, k = 14336 (64 tiles) 100 -> 91, fp8 of 256 rows 102 -> 89.
+// 4096, k = 14336 (64 tiles) 100 -> 91, fp8 of 256 rows 102 -> 89; but with
+// slices of 8 k blocks (2048 rows, n = 1024, k = 8192) 69 -> 71, of 6 54 -> 65.
 constexpr int64_t kWideTiles = 200;
 constexpr int64_t kWideMost = 512;
 constexpr int64_t kWideSupers = 7;
-constexpr int64_t kWideDeep = 60;  // .. kWideMost / kSplitMax tiles
+constexpr int64_t kWideDeep = 60;  // .. kWideMost / kSplitMax tiles,
+constexpr int kWideDeepKb = 96;    // of at least so many k blocks
 
 constexpr int kRouteChunk = 512;  // pairs per routing workgroup
 constexpr size_t kNone = (size_t)-1;

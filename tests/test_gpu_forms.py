@@ -160,12 +160,12 @@ def _linear_items(s, m, n, k):
     (W.W4A4, 31, 1040, 512, 4), (W.FP8, 1984, 4096, 256, 1), (W.MXFP4, 2021, 3408, 256, 1),
     (W.FP8, 500, 14336, 128, 1), (W.FP8, 256, 14336, 128, 4), (W.W8A8, 1984, 4096, 256, 4),
     (W.W8A8, 8000, 1024, 256, 1), (W.W4A4G128, 4000, 1024, 256, 4), (W.W4A4G128, 8000, 1024, 256, 1),
-    (W.W8A8, 512, 4096, 6144, 1), (W.W8A8, 512, 4096, 6016, 4), (W.W8A8, 300, 4096, 6144, 4)],
+    (W.W8A8, 512, 4096, 12288, 1), (W.W8A8, 512, 4096, 12160, 4), (W.W8A8, 300, 4096, 12288, 4)],
     ids=lambda v: getattr(v, "name", str(v)))
 def test_linear_form(scheme, m, n, k, items):
     """Launches of few tiles are narrow (items 4); those whose tiles fill the
     chip are not: 200 to 512 tiles in seven super-tiles or more, or 60 to 64
-    of at least 48 k blocks."""
+    of at least 96 k blocks."""
     assert _linear_items(scheme, m, n, k) == items
 
 
