@@ -188,7 +188,22 @@ bool narrow_block(const BlockInfo& bi, int64_t T) {
   return down <= kNarrowTiles && narrow_launch(up, wr / bi.E * live + ws, rows, bi.H / 128, t);
 }
 
-WsLayout layout_of(const BlockInfo& bi, int T, int64_t pmin = kPartialMin) {
+// Upper bound of the floats that a phase's slices can fill: every group's rows
+// and channels rounded up to its tiles, in the most slices its depth allows.
+int64_t partial_use(const BlockInfo& bi, int64_t T) {
+  const int bm = cfg_bm(pick_cfg((int)T, K_W16, 1));  // a group has at most T rows
+  const int64_t P = T * bi.k, live = std::min<int64_t>(bi.E, P), sh = (int64_t)bi.nsh * T;
+  auto use = [&](int64_t groups, int64_t rows, int n, int k, int linears) -> int64_t {
+    const int s = std::min(k / 128 / kSplitMinKb, kSplitMax);
+    return s < 2 ? 0 : (rows + groups * bm) * ((n + 511) / 512 * 512) * linears * s;
+  };
+  return std::max(use(live, P, bi.F, bi.H, 2) + use(bi.nsh, sh, bi.Fsh, bi.H, 2),
+                  use(live, P, bi.H, bi.F, 1) + use(bi.nsh, sh, bi.H, bi.Fsh, 1));
+}
+
+// The one layout of a block's workspace for T tokens; its size does not shrink
+// as T grows (a workspace sized for T serves every smaller batch).
+WsLayout layout_of(const BlockInfo& bi, int T) {
   WsLayout L;
   size_t o = 0;
   auto take = [&](size_t bytes) {
@@ -214,12 +229,12 @@ WsLayout layout_of(const BlockInfo& bi, int T, int64_t pmin = kPartialMin) {
   L.rgw = take(4 * P);
   L.rxs8 = bi.any_x8 ? take(4 * P) : kNone;
   L.rxs4 = bi.any_x4 ? take(4 * P) : kNone;
-  // split-K partial sums: a few times the largest layer output, at least pmin
-  // (small batches: a slice holds whole tiles, however few of their rows are
-  // the group's), at most 512 MB
+  // split-K partial sums: a few times the largest layer output, at most 512
+  // MB; enlarged below (small batches: a slice holds whole tiles, however few
+  // of their rows are the group's)
   L.pfloats = std::min<int64_t>((int64_t)1 << 27,
-                                std::max(pmin, 4 * ((int64_t)P + (int64_t)bi.nsh * T) * std::max(std::max(bi.F, bi.Fsh), bi.H)));
-  L.partial = take(4 * (size_t)L.pfloats);
+                                4 * ((int64_t)P + (int64_t)bi.nsh * T) * std::max(std::max(bi.F, bi.Fsh), bi.H));
+  const size_t pbase = (size_t)L.pfloats;
   L.xq8 = L.xs8 = L.xq4 = L.xs4 = kNone;
   if (bi.any_x8) { L.xq8 = take((size_t)T * bi.H); L.xs8 = take(4 * (size_t)T); }
   if (bi.any_x4) { L.xq4 = take((size_t)T * bi.H); L.xs4 = take(4 * (size_t)T); }
@@ -249,6 +264,13 @@ WsLayout layout_of(const BlockInfo& bi, int T, int64_t pmin = kPartialMin) {
   L.rids = take(4 * P);
   L.rw = take(4 * P);
   L.shw = bi.nsh ? take(4 * (size_t)T * bi.nsh) : kNone;
+  // the partial buffer comes last: up to kPartialMin floats where slices can
+  // use them, as long as the workspace then still fits the scratch array of
+  // the no-allocation forward (a block that fits without them is not refused)
+  const size_t base = align256(o + 4 * pbase), most = MXMOE_NOALLOC_SCRATCH_BYTES;
+  const int64_t spare = base < most ? (int64_t)((most - o) / 4) : 0;
+  L.pfloats = std::max<int64_t>(L.pfloats, std::min(std::min(kPartialMin, partial_use(bi, T)), spare));
+  L.partial = take(4 * (size_t)L.pfloats);
   L.total = o;
   return L;
 }
@@ -626,11 +648,9 @@ mxmoe_status mxmoe_workspace_layout(const mxmoe_block* B, int32_t T, mxmoe_ws_la
   return MXMOE_OK;
 }
 
-// pmin: see layout_of
-static mxmoe_status forward_impl(const mxmoe_block* B, const void* block_table, int32_t T, const void* x,
-                                 const int32_t* topk_ids, const float* topk_w, void* y, void* workspace,
-                                 size_t workspace_bytes, const mxmoe_forward_opts* opts, hipStream_t stream,
-                                 int64_t pmin) {
+mxmoe_status mxmoe_moe_forward_ex(const mxmoe_block* B, const void* block_table, int32_t T, const void* x,
+                                  const int32_t* topk_ids, const float* topk_w, void* y, void* workspace,
+                                  size_t workspace_bytes, const mxmoe_forward_opts* opts, hipStream_t stream) {
   static thread_local BlockInfo bi;
   mxmoe_status st = check_block(B, &bi);
   if (st != MXMOE_OK) return st;
@@ -655,7 +675,7 @@ static mxmoe_status forward_impl(const mxmoe_block* B, const void* block_table, 
   if (!aligned(block_table, 16) || !aligned(x, 16) || !aligned(y, 16) || !aligned(workspace, 256) ||
       !aligned(topk_ids, 4) || !aligned(topk_w, 4))
     return MXMOE_ERR_INVALID_ARG;
-  const WsLayout L = layout_of(bi, T, pmin);
+  const WsLayout L = layout_of(bi, T);
   if (workspace_bytes < L.total) return MXMOE_ERR_WORKSPACE;
 
   uint32_t mask_words[64];
@@ -865,12 +885,6 @@ static mxmoe_status forward_impl(const mxmoe_block* B, const void* block_table, 
   return MXMOE_OK;
 }
 
-mxmoe_status mxmoe_moe_forward_ex(const mxmoe_block* B, const void* block_table, int32_t T, const void* x,
-                                  const int32_t* topk_ids, const float* topk_w, void* y, void* workspace,
-                                  size_t workspace_bytes, const mxmoe_forward_opts* opts, hipStream_t stream) {
-  return forward_impl(B, block_table, T, x, topk_ids, topk_w, y, workspace, workspace_bytes, opts, stream, kPartialMin);
-}
-
 }  // extern "C"
 
 namespace {
@@ -903,17 +917,13 @@ mxmoe_status mxmoe_moe_forward_noalloc(const mxmoe_block* B, const void* block_t
   if (st != MXMOE_OK) return st;
   if (T < 0) return MXMOE_ERR_INVALID_ARG;
   if ((int64_t)T * bi.k >= (1LL << 31)) return MXMOE_ERR_UNSUPPORTED;
-  // the scratch array holds every batch that its size admits without the
-  // partial buffer's lower bound; that bound applies where it still fits
-  int64_t pmin = kPartialMin;
-  if (layout_of(bi, T, pmin).total > (size_t)MXMOE_NOALLOC_SCRATCH_BYTES) pmin = 0;
-  if (layout_of(bi, T, pmin).total > (size_t)MXMOE_NOALLOC_SCRATCH_BYTES) return MXMOE_ERR_WORKSPACE;
+  if (layout_of(bi, T).total > (size_t)MXMOE_NOALLOC_SCRATCH_BYTES) return MXMOE_ERR_WORKSPACE;
   if (T == 0) return MXMOE_OK;
   void* ws = nullptr;
   st = scratch_of_current_device(&ws);
   if (st != MXMOE_OK) return st;
-  return forward_impl(B, block_table, T, x, topk_ids, topk_w, y, ws, (size_t)MXMOE_NOALLOC_SCRATCH_BYTES, nullptr,
-                      stream, pmin);
+  return mxmoe_moe_forward_ex(B, block_table, T, x, topk_ids, topk_w, y, ws, (size_t)MXMOE_NOALLOC_SCRATCH_BYTES,
+                              nullptr, stream);
 }
 
 mxmoe_status mxmoe_moe_forward(const mxmoe_block* B, const void* block_table, int32_t T, const void* x,

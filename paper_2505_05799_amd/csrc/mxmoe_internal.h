@@ -164,10 +164,11 @@ enum PlanField : int32_t {
 constexpr int kSplitExtra = 16384;
 constexpr int kSplitMax = 8;
 
-// Least size of the partial buffer in floats (32 MB).  Sized by the layer's
-// output alone, the buffer of a small batch held the slices of its first
-// groups only: of the Mixtral-shaped block at 32 tokens, half of the down
-// projections (112 k blocks each) ran unsliced and kept the launch going.
+// Size of the partial buffer in floats (32 MB) up to which it holds all that
+// slices can fill.  Sized by the layer's output alone, the buffer of a small
+// batch held the slices of its first groups only: of the Mixtral-shaped block
+// at 32 tokens, half of the down projections (112 k blocks each) ran unsliced
+// and kept the launch going.
 constexpr int64_t kPartialMin = (int64_t)1 << 23;
 
 // Limits of a block: routed experts, shared experts, groups (routed + shared).

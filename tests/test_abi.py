@@ -262,3 +262,41 @@ def test_noalloc_validation(lib):
     assert lib.mxmoe_moe_forward_noalloc(C.byref(B), p, 4096, p, p, p, p, None) == M.ERR_WORKSPACE
     assert lib.mxmoe_moe_forward_noalloc(C.byref(B), p, 0, p, p, p, p, None) == M.OK
     assert lib.mxmoe_moe_forward_noalloc(C.byref(B), p, -1, p, p, p, p, None) == M.ERR_INVALID_ARG
+
+
+def _plain_block(E, k, H, F, n_shared=0, F_shared=0, scheme=W.W8A8):
+    n = 3 * (E + n_shared)
+    schemes = (M.Scheme_t * n)(*[M.scheme_t(scheme)] * n)
+    packed = (C.c_void_p * n)(*[1 << 20] * n)
+    B = M.Block_t(H, F, E, k, n_shared, F_shared, M.BF16, C.cast(schemes, C.POINTER(M.Scheme_t)),
+                  C.cast(packed, C.POINTER(C.c_void_p)))
+    return B, (schemes, packed)
+
+
+@pytest.mark.parametrize("E,k,H,F,n_shared", [(4, 2, 256, 256, 0), (60, 4, 2048, 1408, 4), (8, 2, 4096, 14336, 0),
+                                              (640, 8, 4096, 14336, 0), (700, 8, 8192, 14336, 0),
+                                              (1024, 8, 7168, 2048, 1)])
+def test_workspace_and_scratch_agree(lib, E, k, H, F, n_shared):
+    """The no-allocation forward refuses exactly the batches whose workspace
+    exceeds its array, and a workspace serves every smaller batch.  (x is
+    misaligned: a batch that is not refused fails there, nothing is enqueued.)"""
+    B, keep = _plain_block(E, k, H, F, n_shared, F)
+    p = C.c_void_p(1 << 20)
+    last = 0
+    sizes = sorted({max(1, int(2 ** (i / 4))) for i in range(49)})
+    for T in sizes:
+        size = lib.mxmoe_workspace_bytes(C.byref(B), T)
+        st = lib.mxmoe_moe_forward_noalloc(C.byref(B), p, T, C.c_void_p((1 << 20) + 2), p, p, p, None)
+        assert (st == M.ERR_WORKSPACE) == (size > M.NOALLOC_SCRATCH_BYTES), (T, size, st)
+        assert size >= last, T
+        last = size
+
+
+def test_one_token_workspace_is_small(lib):
+    """Nothing is reserved that a batch cannot use: one token's slices of a
+    Qwen1.5-MoE-shaped block take less than 4 MB of partial sums."""
+    B, keep = _plain_block(60, 4, 2048, 1408, 1, 5632)
+    lay = M.WsLayout_t()
+    assert lib.mxmoe_workspace_layout(C.byref(B), 1, C.byref(lay)) == M.OK
+    assert 4 * lay.partial_floats < 4 << 20
+    assert lib.mxmoe_workspace_bytes(C.byref(B), 1) < 20 << 20
