@@ -505,7 +505,7 @@ def optimal_makespan(costs: Sequence[float], P: int) -> float:
 # Slicing of the reduction (split-K, the paper's slice-K tile parameter):
 #   theta = (sum over the phase's tiles of the unsliced tile cost) // nwg // 2,
 #   nwg the workgroups of the launch; a group takes the fewest slices S in
-#   1 .. Smax = clamp(K/128 // 6, 1, 8) whose tile cost (reduction length
+#   1 .. Smax = clamp(K/128 // min_kb, 1, 8) whose tile cost (reduction length
 #   ceil(K/128 / S) k blocks) is at most theta, else the S of the cheapest tile
 #   (the fewest slices among equals); groups without tiles are not sliced;
 #   budgets, granted in group order: the slices' partial sums (tiles * S * BM *
@@ -514,7 +514,8 @@ def optimal_makespan(costs: Sequence[float], P: int) -> float:
 #   cheapest tile's (none within theta) is sliced only if the phase's unsliced
 #   tiles plus every added tile granted so far plus its own stay within nwg
 #   and no earlier such group failed that test; else S = 1;
-#   a sliced group queues tiles * S tiles.
+#   a sliced group queues tiles * S tiles.  min_kb, the least k blocks of a
+#   slice, is 6; in a launch of the narrow form 12, of a single linear there 8.
 #
 # Tile cost (Sec. 4.2.2: the cost c_t of a tile of each configuration is
 # profiled ahead of time and given to the scheduler): `costs` is that table,
@@ -555,11 +556,11 @@ def _tile_cost(entry, kb: int, split: int, mt: int) -> int:
     return min(max(c, 1), 2 * 10**9)
 
 
-def _choose_split(entry, kblocks: int, mt: int, nt: int, theta: int):
+def _choose_split(entry, kblocks: int, mt: int, nt: int, theta: int, min_kb: int = _SPLIT_MIN_KB):
     """(slices, True if no slice count is within theta)."""
     if mt * nt <= 0:
         return 1, False
-    smax = max(1, min(_SPLIT_MAX, kblocks // _SPLIT_MIN_KB))
+    smax = max(1, min(_SPLIT_MAX, kblocks // min_kb))
     best, cbest = 1, None
     for sp in range(1, smax + 1):
         c = _tile_cost(entry, -(-kblocks // sp), sp, mt)
@@ -570,14 +571,17 @@ def _choose_split(entry, kblocks: int, mt: int, nt: int, theta: int):
     return best, True
 
 
-def tile_plan(ms: Sequence[int], lins: Sequence, phase: int, costs, partial_floats: int = 0, nwg: int = 512):
+def tile_plan(ms: Sequence[int], lins: Sequence, phase: int, costs, partial_floats: int = 0, nwg: int = 512,
+              min_kb: int = _SPLIT_MIN_KB):
     """Tile configuration, tile counts, slices, cost and queue rank per group.
 
     ms[g]: rows of group g; lins[g]: its linear (gate for phase 0, down for 1);
     costs: the tile cost table (see above); partial_floats: size of the
-    split-K partial buffer; nwg: workgroups of the launch.  Returns a list of
-    dicts (cfg, mtiles, ntiles, split, tiles, cost, rank) and the queue order
-    (group indices with tiles, longest tile first).
+    split-K partial buffer; nwg: workgroups of the launch; min_kb: least k
+    blocks of a slice.  Returns a list of dicts (cfg, mtiles, ntiles, split,
+    tiles, cost, rank, and of a sliced group its first partial-sum float pbase
+    and output-tile counter cbase) and the queue order (group indices with
+    tiles, longest tile first).
     """
     out = []
     geo = []
@@ -598,10 +602,11 @@ def tile_plan(ms: Sequence[int], lins: Sequence, phase: int, costs, partial_floa
             work += mt * nt * _tile_cost(entry, lin.k // 128, 1, mt)
             unsliced += mt * nt
     theta = work // nwg // _SPLIT_SHARE
-    pused = eused = 0
+    pused = eused = cused = 0
     stopped = False
     for (cfg, mt, nt, entry), lin in zip(geo, lins):
-        sp, fallback = _choose_split(entry, lin.k // 128, mt, nt, theta)
+        base = {"pbase": 0, "cbase": 0}
+        sp, fallback = _choose_split(entry, lin.k // 128, mt, nt, theta, min_kb)
         if sp > 1:
             need = mt * nt * sp * _TILE_BM[cfg] * _TILE_BN[phase][cfg] * (2 if phase == 0 else 1)
             extra = mt * nt * (sp - 1)
@@ -610,9 +615,11 @@ def tile_plan(ms: Sequence[int], lins: Sequence, phase: int, costs, partial_floa
             if pused + need > partial_floats or eused + extra > _SPLIT_EXTRA or (fallback and stopped):
                 sp = 1
             else:
+                base = {"pbase": pused, "cbase": cused}
                 pused += need
                 eused += extra
-        out.append({"cfg": cfg, "mtiles": mt, "ntiles": nt, "split": sp})
+                cused += mt * nt
+        out.append({"cfg": cfg, "mtiles": mt, "ntiles": nt, "split": sp, **base})
     for r, lin, (_, _, _, entry) in zip(out, lins, geo):
         tiles = r["mtiles"] * r["ntiles"] * r["split"]
         r["tiles"] = tiles

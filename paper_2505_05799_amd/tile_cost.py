@@ -110,16 +110,19 @@ class CostTable:
             out[1] += self.linear_ns(m, cfg.H, F, 1, sch[2])
         return [v / self.P for v in out]
 
-    def block_makespan_ns(self, cfg, counts: Sequence[int], schemes) -> List[float]:
+    def block_makespan_ns(self, cfg, counts: Sequence[int], schemes, min_kb: int = 6) -> List[float]:
         """Modelled Group-GEMM time per phase as the paper defines it before its
         approximation, T = max over workers of the worker's summed tile costs,
         with the tiles dealt the way the kernel deals them: each group's tiles
         sliced along K by the kernel's rule (the fewest slices, at most 8 of at
-        least 6 k blocks, whose cost is within half the mean work per worker,
-        else the cheapest tile's slices as long as the phase keeps at most one
-        tile per worker, up to the first group refused for that), longest first, each to the least loaded of the P
-        workers; a sliced tile pays the table's slice hand-off, and the launch
-        LAUNCH_NS.  Where tiles far outnumber workers this equals sum c_t / P."""
+        least min_kb k blocks, whose cost is within half the mean work per
+        worker, else the cheapest tile's slices as long as the phase keeps at
+        most one tile per worker, up to the first group refused for that),
+        longest first, each to the least loaded of the P workers; a sliced tile
+        pays the table's slice hand-off, and the launch LAUNCH_NS.  Where tiles
+        far outnumber workers this equals sum c_t / P.  min_kb is 6 for
+        launches of planned tiles, which the table's costs describe; narrow
+        ones take 12."""
         out = []
         for ph in (0, 1):
             groups = []
@@ -141,7 +144,7 @@ class CostTable:
             stopped = False
             tiles = []
             for nt, a, b, kb in groups:
-                smax = max(1, min(8, kb // 6))
+                smax = max(1, min(8, kb // min_kb))
                 cost = lambda sl: max(a + b * (-(-kb // sl)), 1e-3) + (self.slice_ns if sl > 1 else 0.0)
                 best, cbest, fallback = 1, None, True
                 for sl in range(1, smax + 1):

@@ -1,7 +1,10 @@
 """The two forms of the Group-GEMM launch (planned tiles, and the narrow items
 that launches with few tiles are cut into) against the oracle, at the edges of
 their tiles: rows around 16 / 32 / 64 / 128, channels around the item widths
-(64, 128) and the tile widths (256, 512), reductions with and without slices."""
+(64, 128) and the tile widths (256, 512), reductions with and without slices
+(of at least 8 k blocks in a narrow linear, 12 in a narrow block); which form a
+launch takes; and the launches in front, routing and the encoding of long
+inputs."""
 
 import numpy as np
 import pytest
@@ -26,6 +29,43 @@ def test_narrow_linear(scheme, m, n, k):
     for act in ("bf16", "fp16"):
         q, a, got, _ = _linear_case(scheme, act, m, n, k, m + n + k)
         _check_linear(q, a, got, act)
+
+
+@pytest.mark.parametrize("scheme", W.ALL_SCHEMES, ids=lambda s: s.name)
+@pytest.mark.parametrize("m,n", [(16, 528), (33, 656), (97, 528), (129, 656)])
+def test_narrow_linear_slices(scheme, m, n):
+    """Slices of several channel items, the last one ragged."""
+    for act in ("bf16", "fp16"):
+        q, a, got, split = _linear_case(scheme, act, m, n, 4096, m + n)
+        assert split >= 2
+        _check_linear(q, a, got, act)
+
+
+@pytest.mark.parametrize("act,T", [("bf16", 9), ("fp16", 70)])
+def test_narrow_block_slices(act, T):
+    """Both launches narrow and several of their groups sliced: the plan's
+    records against the oracle's with 12 k blocks a slice (and a partial buffer
+    that refuses no slice), each group with areas and counters of its own, and
+    the block against the oracle."""
+    from tests.test_gpu_configs import PF_N, plan_misc
+    torch = torch_mod()
+    sch = [(W.W4G128, W.W4G128, W.W3G128), (W.W8A8, W.W8A8, W.FP8), (W.W3G128, W.W3G128, W.W4A4G128)]
+    blk = W.random_small_block(77 + T, T=T, H=3072, F=3072, E=2, k=1, n_shared=1, F_shared=3200, act=act, schemes=sch)
+    mb, y = run_block(blk)
+    lay = mb.workspace_layout(T)
+    misc = plan_misc(mb, T, 3, lay["plan_queue_cap"])
+    assert misc[9] == 4
+    rec = mb.ws_view("plan", torch.int32, 2 * 3 * PF_N, T).cpu().numpy().reshape(2, 3, PF_N)
+    ms = [int((blk.topk_ids == e).sum()) for e in range(2)] + [T]
+    for ph in (0, 1):
+        lins = [blk.linears[g][0 if ph == 0 else 2] for g in range(3)]
+        want, _ = O.tile_plan(ms, lins, ph, M.get_tile_costs(), partial_floats=1 << 40, nwg=int(misc[8]), min_kb=12)
+        assert sum(w["split"] > 1 for w in want) >= 2
+        for g, w in enumerate(want):
+            got = dict(zip(("m", "cfg", "mtiles", "ntiles", "cost", "rank", "split", "pbase", "cbase"),
+                           rec[ph, g][[1, 2, 3, 4, 6, 7, 8, 9, 10]].tolist()))
+            assert got == {"m": ms[g], **{f: w[f] for f in got if f != "m"}}, (ph, g)
+    say(f"T={T} {act}: {check_forward(mb, blk, y).line()}")
 
 
 @pytest.mark.parametrize("scheme", W.ALL_SCHEMES, ids=lambda s: s.name)
