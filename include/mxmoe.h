@@ -365,7 +365,9 @@ typedef struct {
   size_t partial_floats;/* size of that buffer (floats)                      */
   size_t rsx;           /* fp32 [T, H/128]: row sums of x per 128-wide block
                            (bf16 blocks with 2/3/4-bit gate|up), else -1    */
-  size_t rsh;           /* fp32 [T*k, F/128]: same for routed h, else -1     */
+  size_t rsh;           /* fp32 [T*k, F/128]: same for routed h, else -1; not
+                           written where the launches take the narrow form
+                           (misc[9] of the plan is 4), nor is rsh_shared     */
   size_t rsh_shared;    /* fp32 [n_shared*T, F_shared/128], else -1          */
   size_t xq4g, xs4g;    /* int8 [T,H], fp32 [T, H/128]: x codes for w4a4-g128
                            gate|up (else -1)                                  */

@@ -765,6 +765,8 @@ mxmoe_status mxmoe_moe_forward_ex(const mxmoe_block* B, const void* block_table,
     xp.q4 = at<int8_t>(workspace, L.xq4);
     xp.s4 = at<float>(workspace, L.xs4);
   }
+  // (narrow items sum the rows themselves; the buffer is filled all the same,
+  // beside the planning, for the readers of the workspace layout)
   if (bi.rs_x) xp.rs = at<float>(workspace, L.rsx);
   if (bi.any_x4g) {
     xp.q4g = at<int8_t>(workspace, L.xq4g);

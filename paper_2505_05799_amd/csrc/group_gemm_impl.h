@@ -2,16 +2,19 @@
 // micro-kernel specialization, equal-resource tile configurations, and a
 // greedy longest-tile-first schedule), written for gfx950.
 //
-//   plan_kernel        one workgroup: per (phase, expert) group picks a tile
+//   plan_kernel        one workgroup per phase: per group (expert) picks a tile
 //                      configuration from the group's row count, counts its
 //                      tiles, estimates a per-tile cost and orders the groups by
-//                      decreasing tile cost (ties: lower expert first).  The tile
-//                      queue of a phase is the concatenation of the groups'
-//                      tiles in that order: workgroups that free up take the next
-//                      tile, i.e. list scheduling with the longest tiles first.
-//   group_gemm_kernel  persistent: every workgroup pops tile indices from an
-//                      atomic head counter and dispatches, outside the MAC loop,
-//                      to the micro-kernel of the tile's (scheme, configuration).
+//                      decreasing tile cost (ties: lower expert first).  The tiles
+//                      are dealt to eight queues, one per XCD, in that order:
+//                      workgroups that free up take the next tile, i.e. list
+//                      scheduling with the longest tiles first.
+//   group_gemm_kernel  persistent: a workgroup starts on a tile fixed by its
+//                      index, takes the later ones from its XCD's atomic head
+//                      counter (then from the other queues') and dispatches,
+//                      outside the MAC loop, to the micro-kernel of the tile's
+//                      (scheme, configuration).  The narrow form takes a quarter
+//                      of a tile at a time, an item.
 //
 // Every configuration uses 4 wavefronts (equal resources for all micro-kernels,
 // as the paper requires for horizontal fusion) stacked along the output
@@ -198,8 +201,6 @@ template <int KD> MXMOE_INL u32x4 load_step(const uint8_t* p, int j) {
   }
 }
 
-// Wait until at most N vector-memory loads of this wavefront are outstanding
-// (loads complete in issue order), leaving LDS and export counters alone.
 // An empty statement that reads a value: the compiler waits for the loads of
 // its registers before it.
 MXMOE_INL void touch(uint32_t v) { asm volatile("" ::"v"(v)); }
@@ -214,6 +215,8 @@ template <int KD> MXMOE_INL void touch_raw(const Raw<KD>& r) {
   else touch(r.d[0]);
 }
 
+// Wait until at most N vector-memory loads of this wavefront are outstanding
+// (loads complete in issue order), leaving LDS and export counters alone.
 template <int N> MXMOE_INL void wait_vmem() {
   static_assert(N >= 0 && N < 64, "vmcnt is six bits");
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
@@ -618,7 +621,7 @@ MXMOE_INL void run_tile(Smem<NAR>& sm, const GemmArgs& a, const DevExpert* ex, i
   const int kblocks = K / 128;
   // split-K: queued channel tile ntv = slice * (channel tiles) + channel tile;
   // the slice reduces k blocks [kb0, kb1), balanced so that every slice is
-  // non-empty (the plan only slices when there are >= 6 k blocks per slice)
+  // non-empty (the plan's slices have at least kSplitMinKb k blocks)
   const int bnw = NAR ? narrow_bn(pcfg, BN) : BN;  // channels of the planned tile
   const int ntr = (N + bnw - 1) / bnw;
   const int slice = split > 1 ? ntv / ntr : 0;

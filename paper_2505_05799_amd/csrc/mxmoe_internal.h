@@ -527,7 +527,7 @@ hipError_t launch_plan(const DevExpert* experts, int E, int G, int T, const Rout
 void tile_costs_default(TileCosts* out);
 void tile_costs_set(const TileCosts* t);
 void tile_costs_get(TileCosts* out);
-// grid: workgroups of the wide form; narrow: the narrow form, on twice as many
+// grid: workgroups of the wide form, two per CU; narrow: the narrow form, on three
 hipError_t launch_group_gemm(const GemmArgs& a, int phase, int grid, bool narrow, hipStream_t s);
 int group_gemm_grid(int device);
 
