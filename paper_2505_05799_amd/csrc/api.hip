@@ -145,27 +145,31 @@ int64_t tiles_bound(int64_t groups, int64_t rows, int n, int bn) {
   return (groups + rows / 64) * ((n + bn - 1) / bn);
 }
 // A launch's tiles and super-tiles as the plan cuts them if the rows are spread
-// evenly; heavy: tiles with those of w4a4-g128 counted half.
+// evenly; load: the tiles as twentieths of a 128-row tile's worth (kWideTiles).
 struct TileGuess {
-  int64_t tiles = 0, heavy = 0, supers = 0;
+  int64_t tiles = 0, load = 0, supers = 0;
   void add(int64_t rows, int n, int kd, int bn_phase) {
     const int c = pick_cfg((int)rows, kd, 0);
     const int64_t mt = (rows + cfg_bm(c) - 1) / cfg_bm(c), nt = (n + cfg_bn(c, bn_phase) - 1) / cfg_bn(c, bn_phase);
     const int64_t sm = std::min<int64_t>(mt, 8), sn = std::min(nt, kSuperTiles / sm);
     tiles += mt * nt;
-    heavy += kd == K_W4A4G ? mt * nt / 2 : mt * nt;
+    load += mt * nt * (kd == K_W4A4G ? 16 : kd == K_F8A8 || kd == K_MXFP4 ? 25 : 20);
     supers += ((mt + sm - 1) / sm) * ((nt + sn - 1) / sn);
   }
 };
 // The narrow form takes launches with few tiles, and those up to kNarrowTiles
-// whose tiles stream many weight bytes, unless the tiles fill the chip as they
-// are (kWideTiles).  rows: of a group, in the mean; kb: k blocks.
-bool narrow_launch(int64_t tiles, int64_t weight_bytes, int64_t rows, int kb, const TileGuess& t) {
-  if (rows > 32) {
-    if (t.heavy >= kWideTiles && t.tiles <= kWideMost && t.supers >= kWideSupers) return false;
-    if (t.tiles >= kWideDeep && t.tiles * kSplitMax <= kWideMost && kb >= kWideDeepKb) return false;
-  }
+// whose tiles stream many weight bytes (unless the tiles fill the chip as they
+// are, below).
+bool narrow_launch(int64_t tiles, int64_t weight_bytes) {
   return tiles <= kNarrowFew || (tiles <= kNarrowTiles && weight_bytes >= tiles * kNarrowBytes);
+}
+bool narrow_linear(int kd, int m, int n, int k) {
+  TileGuess t;
+  t.add(m, n, kd, 1);
+  if (m > 32 && t.load >= 20 * kWideTiles && t.tiles <= kWideMost) return false;
+  const bool deep = k / 128 >= kWideDeepKb && (kd == K_W16 || kd == K_W8A8 || kd == K_F8A8);
+  if (m > 32 && deep && t.tiles >= kWideDeep && t.tiles * kSplitMax <= kWideMost) return false;
+  return narrow_launch(tiles_bound(1, m, n, 256), codes_bytes(kd, n, k));
 }
 // Whether the block's Group-GEMM launches take the narrow form (decided on the
 // gate|up launch; the routed experts' weights count by the share of experts
@@ -183,9 +187,11 @@ bool narrow_block(const BlockInfo& bi, int64_t T) {
     (routed ? tr : t).add(routed ? rows : T, routed ? bi.F : bi.Fsh, bi.kinds[g][0], 0);
   }
   t.tiles += tr.tiles * live / bi.E;
-  t.heavy += tr.heavy * live / bi.E;
+  t.load += tr.load * live / bi.E;
   t.supers += tr.supers * live / bi.E;
-  return down <= kNarrowTiles && narrow_launch(up, wr / bi.E * live + ws, rows, bi.H / 128, t);
+  if (rows >= kWideRows && t.load >= 20 * kWideTiles && t.tiles <= kWideMostRouted && t.supers >= kWideSupers)
+    return false;
+  return down <= kNarrowTiles && narrow_launch(up, wr / bi.E * live + ws);
 }
 
 // Upper bound of the floats that a phase's slices can fill: every group's rows
@@ -507,9 +513,7 @@ mxmoe_status mxmoe_linear_forward(const mxmoe_linear* L, mxmoe_dtype act, const 
   ga.partial = at<float>(workspace, w.partial);
   // the input's encoding rides on the plan launch (its spare workgroups), or
   // takes a launch of its own (encode_apart)
-  TileGuess tg;
-  tg.add(m, L->n, kd, 1);
-  const bool narrow = narrow_launch(tiles_bound(1, m, L->n, 256), codes_bytes(kd, L->n, L->k), m, L->k / 128, tg);
+  const bool narrow = narrow_linear(kd, m, L->n, L->k);
   XPrep xp;
   memset(&xp, 0, sizeof(xp));
   xp.x = a;

@@ -321,29 +321,33 @@ constexpr int64_t kNarrowFew = 512;
 constexpr int64_t kNarrowTiles = 2048;
 constexpr int64_t kNarrowBytes = 192 << 10;
 static_assert(4 * kNarrowTiles <= kSplitExtra, "arrival counters of narrow items");
-// Of those, the launches whose groups have more than 32 rows and whose tiles
-// (estimated from evenly spread rows) fill the chip by themselves stay wide:
-// from kWideTiles to the 512 resident workgroups, in enough super-tiles that
-// every XCD's queue gets its share (with fewer, XCDs idle and the narrow
-// form's even deal wins: a w16 linear of 1984 rows, n = k = 4096, 256 tiles in
-// four super-tiles, 172 -> 118 us narrow).  A narrow item's MFMAs share a weight
-// fragment between half as many rows.  Narrow -> wide: fp8 linears of 1984
-// rows, n = 4096 (496 tiles), k = 4096 85 -> 60 us, k = 14336 312 -> 175; mxfp4
-// 64 -> 47, 202 -> 148; w16, 8000 rows, n = 1024, 124 -> 92; blocks of 16
-// experts of 768, 700 tokens (228 tiles), 162 -> 141 (w16) and 108 -> 92 (fp8);
-// 11 experts of 1280, 2329 tokens, fp8 168 -> 113.  On the other side: 4 experts
-// of 1408, 2500 tokens (220 tiles in four super-tiles), w8a8 90 -> 110; 156
-// tiles (9 experts of 1536, w3g128) 0.7 of the wide time.  A w4a4-g128 tile
-// counts half: its group rescale costs more per row, and at 252 tiles the
-// narrow form still wins (52 against 61 us), at 496 the wide (79 -> 71).
-// A few deep tiles fill the workgroups in kSplitMax slices: w8a8, 512 rows, n =
-// 4096, k = 14336 (64 tiles) 100 -> 91, fp8 of 256 rows 102 -> 89; but with
-// slices of 8 k blocks (2048 rows, n = 1024, k = 8192) 69 -> 71, of 6 54 -> 65.
-constexpr int64_t kWideTiles = 200;
+// Of those, the launches whose planned tiles fill the chip by themselves stay
+// wide (a narrow item's MFMAs share a weight fragment between half as many
+// rows).  A single linear: from kWideTiles to the 512 resident workgroups, in
+// tiles of 128 rows; an FP8 or MXFP4 tile (64 rows) counts 5/4, a w4a4-g128 tile
+// (64 rows and a rescale per group) 4/5.  Wide over narrow time, 1300 linears of
+// 33 to 4096 rows: at 200 to 255 such tiles 1.0 to 1.4 (w16, w8a8, w4a4, wN), 256
+// to 319 0.9 to 1.24, from there on 0.81 in the mean and 1.03 at most (547
+// linears).  Fp8 of 1984 rows, n = 4096 (496 tiles): k = 4096 85 -> 60 us, k =
+// 14336 312 -> 175; mxfp4 64 -> 47, 202 -> 148.
+constexpr int64_t kWideTiles = 320;
 constexpr int64_t kWideMost = 512;
-constexpr int64_t kWideSupers = 7;
+// A few deep tiles of 8- and 16-bit weights fill the workgroups in kSplitMax
+// slices: w8a8, 512 rows, n = 4096, k = 14336 (64 tiles) 100 -> 91 us, fp8 of 256
+// rows 102 -> 89, w16 0.81 to 0.95; w3g128 and w4a4 on FP6 lose 6%, and so do
+// slices of 8 k blocks (2048 rows, n = 1024, k = 8192 w8a8 69 -> 71), of 6 54 -> 65.
 constexpr int64_t kWideDeep = 60;  // .. kWideMost / kSplitMax tiles,
 constexpr int kWideDeepKb = 96;    // of at least so many k blocks
+// A block's tiles depend on the routing, which the host does not know.  Skewed,
+// a group has a last tile of few rows and a few groups hold most of the work:
+// of 350 blocks with 200 to 512 estimated tiles 40% were slower in the wide form,
+// up to 1.4 times (22 experts of 640, 308 tokens, fp8 81 -> 97 us).  From
+// kWideRows rows per expert on, and with some room below the 512 workgroups,
+// it holds: 0.90 of the narrow time in the mean (43 blocks), 1.01 at most.
+// kWideSupers: every XCD's queue gets its share of the tiles.
+constexpr int64_t kWideRows = 512;
+constexpr int64_t kWideMostRouted = 480;
+constexpr int64_t kWideSupers = 10;
 
 constexpr int kRouteChunk = 512;  // pairs per routing workgroup
 constexpr size_t kNone = (size_t)-1;

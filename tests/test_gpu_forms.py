@@ -198,22 +198,24 @@ def _linear_items(s, m, n, k):
 
 @pytest.mark.parametrize("scheme,m,n,k,items", [
     (W.W4A4, 31, 1040, 512, 4), (W.FP8, 1984, 4096, 256, 1), (W.MXFP4, 2021, 3408, 256, 1),
-    (W.FP8, 500, 14336, 128, 1), (W.FP8, 256, 14336, 128, 4), (W.W8A8, 1984, 4096, 256, 4),
-    (W.W8A8, 8000, 1024, 256, 1), (W.W4A4G128, 4000, 1024, 256, 4), (W.W4A4G128, 8000, 1024, 256, 1),
-    (W.W8A8, 512, 4096, 12288, 1), (W.W8A8, 512, 4096, 12160, 4), (W.W8A8, 300, 4096, 12288, 4)],
+    (W.FP8, 500, 8192, 128, 1), (W.FP8, 500, 7936, 128, 4), (W.W8A8, 1984, 4096, 256, 4),
+    (W.W8A8, 100, 81920, 1536, 1), (W.W8A8, 100, 81664, 1536, 4),
+    (W.W4A4G128, 6400, 1024, 256, 1), (W.W4A4G128, 6300, 1024, 256, 4),
+    (W.W4A4F6, 512, 4096, 12288, 4), (W.W8A8, 512, 4096, 12288, 1), (W.W8A8, 512, 4096, 12160, 4), (W.W8A8, 300, 4096, 12288, 4)],
     ids=lambda v: getattr(v, "name", str(v)))
 def test_linear_form(scheme, m, n, k, items):
     """Launches of few tiles are narrow (items 4); those whose tiles fill the
-    chip are not: 200 to 512 tiles in seven super-tiles or more, or 60 to 64
-    of at least 96 k blocks."""
+    chip are not: 320 to 512 (256 of FP8 and MXFP4, 400 of w4a4-g128), or 60 to
+    64 of 8- or 16-bit weights and at least 96 k blocks."""
     assert _linear_items(scheme, m, n, k) == items
 
 
-@pytest.mark.parametrize("T,items", [(2000, 4), (3200, 1)])
-def test_block_form(T, items):
-    """8 experts of 4 channel tiles: 4 row tiles each (128 tiles), or 7 (224)."""
+@pytest.mark.parametrize("E,T,items", [(8, 2048, 4), (8, 2300, 1), (10, 2550, 4), (10, 2560, 1)])
+def test_block_form(E, T, items):
+    """Experts of 4 channel tiles of FP8, which leave the narrow form at 512 rows
+    each, 256 tiles and ten super-tiles (a ninth row tile begins another)."""
     from tests.test_gpu_configs import plan_misc
-    blk = W.random_small_block(T, T=T, H=256, F=512, E=8, k=2, act="bf16", schemes=[(W.W8A8,) * 3] * 8)
+    blk = W.random_small_block(T, T=T, H=256, F=512, E=E, k=2, act="bf16", schemes=[(W.FP8,) * 3] * E)
     mb, y = run_block(blk)
-    assert plan_misc(mb, T, 8, mb.workspace_layout(T)["plan_queue_cap"])[9] == items
-    say(f"T={T}: {check_forward(mb, blk, y).line()}")
+    assert plan_misc(mb, T, E, mb.workspace_layout(T)["plan_queue_cap"])[9] == items
+    say(f"E={E} T={T}: {check_forward(mb, blk, y).line()}")
